@@ -91,14 +91,14 @@ def draw(rng):
     grid = rng.randint(4, 16)
     n_r = rng.choice([d for d in (1, 2, 3, 4, 5) if grid % d == 0])
     cap = int(round(math.exp(rng.uniform(math.log(24), math.log(512)))))
-    if op == "map_feedback":
-        grid = min(grid, 12)
-        cap = min(cap, 512 - grid * grid)
+    tau = rng.choice([3, 3, 3, 5, 10])
+    if op in ("map", "map_feedback"):  # a frame's voxels hold a scan's few points: they must reach tau to be solved
+        grid, cap, tau, voxel = min(grid, 12), min(cap, 128), min(tau, 5), max(voxel, 0.25)
     scan = "spin"
     if op in ("frame", "fit", "voxelize") and rng.random() < 0.3:
         scan = rng.choice(["mixed", "aggregated"])
     return _case(None, op, scan=scan, beams=beams, azimuths=az, frames=frames, voxel=voxel, cap=cap,
-                 tau=rng.choice([3, 3, 3, 5, 10]), grid=grid, ell=round(voxel * rng.uniform(0.3, 0.7), 4),
+                 tau=tau, grid=grid, ell=round(voxel * rng.uniform(0.3, 0.7), 4),
                  ls_mode=rng.choice([0, 0, 1]), frame_mode=rng.choice([0, 0, 0, 1]) if op in ("frame", "fit") else 0,
                  precision=rng.choice(["fp32", "fp32", "fp64"]), point_noise=op == "fit" and rng.random() < 0.3,
                  n_r=n_r, cell=round(max(0.03, voxel * n_r / grid * rng.uniform(1.0, 3.0)), 3))
@@ -286,6 +286,7 @@ def prepare(case, seed):
     if op in ("map", "map_feedback"):
         s["frames"] = _frames(c, seed)
         s["out"] = _update_buffers(c, s["frames"])
+        s["max_voxels"] = len(_group(torch.cat(s["frames"]), c["voxel"])["cnt"]) * 5 // 4
         s["ctx"] = _context(c, p)
         return s
     if op == "gauss":
@@ -318,7 +319,7 @@ def prepare(case, seed):
 def run(s):
     op, ctx, p, c = s["op"], s["ctx"], s["p"], s["c"]
     if op in ("map", "map_feedback"):
-        m = vgpr.Map(ctx, p, max_voxels=100_000, feedback=op == "map_feedback")
+        m = vgpr.Map(ctx, p, max_voxels=s["max_voxels"], feedback=op == "map_feedback")
         n_upd = []
         for f, out in zip(s["frames"], s["out"]):
             n_upd.append(len(m.update(f, cap_upd=len(out[0]), out=out)[0]))
