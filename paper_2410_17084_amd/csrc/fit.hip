@@ -1040,22 +1040,8 @@ __global__ void __launch_bounds__(kBlockThreads) fit_block_kernel(FitParams P, F
 }
 
 // ---------------------------------------------------------------------------
-// 2c. tiled solver (FP64, n up to 512): one voxel per workgroup of eight
-//     wavefronts, 32 x 32 tiles, tile products on the FP64 matrix cores
+// 2c. strip solver (FP64, 17 to 512 points) on the FP64 matrix cores
 // ---------------------------------------------------------------------------
-// The augmented system is processed one block of 32 rows at a time, data rows
-// first, then query rows: left-looking across row blocks and right-looking
-// inside one,
-//     L(I,J) = (A(I,J) - sum_{K<J} L(I,K) L(J,K)^T) L(J,J)^-T,
-// the Cholesky factor of K + S tile by tile. The current row block lives in
-// LDS. Finished data tiles L(I,J) and the inverses L(J,J)^-1 of the diagonal
-// tiles go to the workgroup's scratch area, stored in matrix-core operand
-// order so that a wavefront reads one operand fragment as 512 contiguous
-// bytes. The right-hand side gives y = L^-1 f~ one block at a time, query rows
-// become z_q = L^-1 k*_q, and
-//     var_q = s_f^2 - |z_q|^2,   mean_q = mu + z_q . y      (Eq. (3)).
-// Padding rows and columns of the last data block are identity rows, so they
-// leave the factor of the real block unchanged.
 // Order LDS writes of one wavefront before its later reads (no workgroup barrier).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1064,387 +1050,14 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
-constexpr int kTile = 32;
-constexpr int kTileThreads = 512;
-constexpr int kTileWaves = kTileThreads / 64;
-constexpr int kTileDoubles = kTile * kTile;
-constexpr int kXS = kTile + 1;  // row stride of the finished-tile buffer
-constexpr int kQTiles = 8;             // 16-query column tiles per wavefront in the query product
-constexpr int kQGroup = 16 * kQTiles;  // queries per group of the query product
-constexpr int kQTabRows = 12;          // grid rows a group of 128 queries spans (at most 11 for n_q <= 16)
 
+// Accumulator layout of the 16 x 16 x 4 FP64 product: lane l, register k holds element
+// (l / 16 + 4 k, l % 16) of the result; lane l gives A(l % 16, l / 16) and B(l / 16, l % 16).
 __device__ __forceinline__ dbl4 mfma_f64(double a, double b, dbl4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Accumulator layout of the 16 x 16 x 4 FP64 product: lane l, register k holds
-// element (l / 16 + 4 k, l % 16) of the 16 x 16 result.
-//
-// Element (row, col) of a 32 x 32 tile in operand order: fragment (row half h,
-// column quad s) is 64 consecutive doubles, lane l holding (16 h + l % 16, 4 s + l / 16).
-__device__ __forceinline__ int frag_pos(int row, int col) {
-  return (((row >> 4) * 8 + (col >> 2)) << 6) + (row & 15) + ((col & 3) << 4);
-}
-
-// Scratch doubles per workgroup: the lower data tiles and one inverse per diagonal tile.
-constexpr size_t tile_scratch_doubles(int npad) {
-  return (size_t)((npad / kTile) * (npad / kTile + 1) / 2 + npad / kTile) * kTileDoubles;
-}
-
-// Scratch doubles per workgroup of the mixed solver: FP32 lower tiles of L, inverses of the
-// diagonal tiles, and the lower tiles of L^-1 twice (row-major, and in matrix-core operand order).
-constexpr size_t tile_scratch_doubles_mixed(int npad) {
-  return ((size_t)(3 * ((npad / kTile) * (npad / kTile + 1) / 2) + npad / kTile) * kTileDoubles + 1) / 2;
-}
-
-// f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): a loop whose
-// index is a compile-time constant in every iteration.
-template <typename F, int... T>
-__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, T...>) {
-  (f(std::integral_constant<int, T>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
-__device__ __forceinline__ double sum16(double v) {
-#pragma unroll
-  for (int d = 8; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-
-template <int NPAD>
-__global__ void __launch_bounds__(kTileThreads) fit_tile_kernel(FitParams P, FitArgs io,
-                                                                const SlotRec* __restrict__ recs,
-                                                                const RotRec* __restrict__ rots,
-                                                                const float4* __restrict__ staged,
-                                                                const uint32_t* __restrict__ count,
-                                                                uint32_t* __restrict__ next,
-                                                                const int32_t* __restrict__ order,
-                                                                double* __restrict__ scratch) {
-  constexpr int NB = NPAD / kTile;
-  constexpr int LD = NPAD + 2;  // row stride of the row block, in doubles
-  // up to 128 points every finished tile and diagonal inverse stays in LDS (no scratch traffic)
-  constexpr bool kLdsTiles = NPAD <= 128;
-  __shared__ double s_tiles[kLdsTiles ? (NB * (NB + 1) / 2 + NB) * kTileDoubles : 1];
-  __shared__ double rb[kTile * LD];
-  __shared__ double xb[kTile * kXS];  // the tile finished in the current step
-  __shared__ double pu[NPAD], pw[NPAD], pf[NPAD];
-  __shared__ float pn[NPAD];
-  __shared__ double sy[NPAD];
-  __shared__ double srhs[kTile], squ[kTile], sqw[kTile];
-  __shared__ double sdc[2 * kTile + 8];  // diagonal-tile column broadcast (lanes >= 32 hold zeros)
-  __shared__ double srd[kTile];          // 1 / L_jj of the diagonal tile
-  __shared__ double sdy;
-  __shared__ int s_item, s_fail;
-  __shared__ unsigned s_maxvar;
-
-  const int tid = threadIdx.x;
-  const int lane = lane_id();
-  const int wid = tid >> 6;
-  const int l16 = lane & 15, l4 = lane >> 4;
-  double* __restrict__ Lt = kLdsTiles ? s_tiles : scratch + (size_t)blockIdx.x * tile_scratch_doubles(NPAD);
-  double* __restrict__ Wt = Lt + (size_t)(NB * (NB + 1) / 2) * kTileDoubles;
-  const int cnt_items = (int)*count;
-  const double sf2 = (double)P.sf2;
-
-  for (;;) {
-    if (tid == 0) {
-      s_item = (int)atomicAdd(next, 1u);
-      s_fail = 0;
-      s_maxvar = 0u;
-    }
-    __syncthreads();
-    if (s_item >= cnt_items) break;
-    const int item = order ? order[s_item] : s_item;  // slot of the voxel
-    const SlotRec r = recs[item];
-    const FrameRec& fr = r.fr;
-    const RotRec* rot = rots ? rots + item : nullptr;
-    const int n = fr.n;
-    const int ax = fr.axes & 3, u = (fr.axes >> 2) & 3, wax = (fr.axes >> 4) & 3;
-    const double lam = fr.lam;
-    for (int i = tid; i < NPAD; i += kTileThreads) {
-      double xu = 0, xw = 0, fv = 0;
-      float nz = 0.f;
-      if (i < n) {
-        const float4 pt = staged[r.off + i];
-        local_point(P, fr, rot, pt, &xu, &xw, &fv);
-        nz = pt.w;
-      }
-      pu[i] = xu;
-      pw[i] = xw;
-      pf[i] = fv;
-      pn[i] = nz;
-    }
-    const int nbd = (n + kTile - 1) / kTile;
-    const int nbe = (P.m + kTile - 1) / kTile;
-    // entry (rr, c) of row block Ib of the augmented system: K + S for data blocks (identity
-    // rows and columns past n), K*^T for query blocks (zero past the grid and past n)
-    auto entry = [&](int Ib, int rr, int c) -> double {
-      if (Ib < nbd) {
-        const int i = Ib * kTile + rr;
-        if (i < n && c < n) {
-          const double du = pu[i] - pu[c], dw = pw[i] - pw[c];
-          return sf2 * exp(-(du * du + dw * dw) * lam) + (i == c ? (double)pn[i] : 0.0);
-        }
-        return i == c ? 1.0 : 0.0;
-      }
-      const int q = (Ib - nbd) * kTile + rr;
-      if (q < P.m && c < n) {
-        const double du = squ[rr] - pu[c], dw = sqw[rr] - pw[c];
-        return sf2 * exp(-(du * du + dw * dw) * lam);
-      }
-      return 0.0;
-    };
-    // query coordinates of the first query block now: its rows are built in part during the
-    // last data block's diagonal phase
-    if (tid < kTile) {
-      float gu = 0.f, gw = 0.f;
-      if (tid < P.m) query_coords(P, fr, tid, &gu, &gw);
-      squ[tid] = (double)gu - fr.anc_u;
-      sqw[tid] = (double)gw - fr.anc_w;
-    }
-    int c_pre = 0;  // columns [0, c_pre) of block I were built during the previous diagonal phase
-    for (int I = 0; I < nbd + nbe; ++I) {
-      const bool data = I < nbd;
-      const int ncols = data ? (I + 1) * kTile : nbd * kTile;
-      if (I > nbd && tid < kTile) {
-        const int q = (I - nbd) * kTile + tid;
-        float gu = 0.f, gw = 0.f;
-        if (q < P.m) query_coords(P, fr, q, &gu, &gw);
-        squ[tid] = (double)gu - fr.anc_u;
-        sqw[tid] = (double)gw - fr.anc_w;
-      }
-      __syncthreads();
-      // the block's rows of the augmented system (the columns not built ahead)
-      {
-        // thread t fills row t % 32, every 16th column from c_pre + t / 32
-        const int rr = tid & (kTile - 1);
-        for (int c = c_pre + tid / kTile; c < ncols; c += kTileThreads / kTile) rb[rr * LD + c] = entry(I, rr, c);
-      }
-      c_pre = 0;
-      __syncthreads();
-      const int jend = data ? I : nbd;
-      // operand fragment of L(J,J)^-1 for this wavefront's quarter of X, fetched one step ahead
-      // (the fetch of step J + 1 is in flight during step J's updates and barriers)
-      double wfn[8];
-      if (wid < 4 && jend > 0) {
-#pragma unroll
-        for (int s = 0; s < 8; ++s) wfn[s] = Wt[(((wid & 1) * 8 + s) << 6) + lane];
-      }
-      for (int J = 0; J < jend; ++J) {
-        // finish tile J: X = A(I,J) L(J,J)^-T, one 16 x 16 quarter on each of
-        // wavefronts 0-3, into the tile buffer (the row block is still being read)
-        dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-        const int a = (wid >> 1) & 1, b = wid & 1;
-        if (wid < 4) {
-#pragma unroll
-          for (int s = 0; s < 8; ++s) acc = mfma_f64(rb[(a * 16 + l16) * LD + J * kTile + 4 * s + l4], wfn[s], acc);
-          if (J + 1 < jend) {
-            const double* __restrict__ W = Wt + (size_t)(J + 1) * kTileDoubles;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) wfn[s] = W[((b * 8 + s) << 6) + lane];
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) xb[(a * 16 + l4 + 4 * k) * kXS + b * 16 + l16] = acc[k];
-        }
-        __syncthreads();
-        if (wid < 4) {
-          double* __restrict__ Lij = Lt + (size_t)(I * (I + 1) / 2 + J) * kTileDoubles;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int row = a * 16 + l4 + 4 * k, col = b * 16 + l16;
-            rb[row * LD + J * kTile + col] = acc[k];
-            if (data) Lij[frag_pos(row, col)] = acc[k];
-          }
-        }
-        // right-looking update of the block's later tiles: A(I,J') -= X L(J',J)^T. With the
-        // tiles in scratch a unit is a 32 x 16 column half (both row halves share the operand
-        // fragment of L(J',J), fetched once); with the tiles in LDS, a 16 x 16 quarter (twice
-        // the units to spread over the wavefronts). The next unit's operand is fetched while
-        // the current one runs.
-        constexpr int kHalves = kLdsTiles ? 1 : 2;  // row halves per unit
-        constexpr int kUnitsPerTile = 4 / kHalves;
-        const int jlast = data ? I : nbd - 1;
-        const int units = (jlast - J) * kUnitsPerTile;
-        int un = wid;
-        double bf[8], bn[8];
-        auto fetch = [&](int uu, double* dst) {
-          const int Jp = J + 1 + uu / kUnitsPerTile, b2 = uu & 1;
-          if (data && Jp == I) {  // L(I,J) itself: the tile buffer
-#pragma unroll
-            for (int s = 0; s < 8; ++s) dst[s] = xb[(b2 * 16 + l16) * kXS + 4 * s + l4];
-          } else {
-            const double* __restrict__ Lpj = Lt + (size_t)(Jp * (Jp + 1) / 2 + J) * kTileDoubles;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) dst[s] = Lpj[((b2 * 8 + s) << 6) + lane];
-          }
-        };
-        if (un < units) fetch(un, bf);
-        for (; un < units; un += kTileWaves) {
-          if (un + kTileWaves < units) fetch(un + kTileWaves, bn);
-          const int Jp = J + 1 + un / kUnitsPerTile, b2 = un & 1;
-          const int a0 = kHalves == 2 ? 0 : (un >> 1) & 1;  // first row half of the unit
-          double* __restrict__ cp = rb + Jp * kTile + b2 * 16 + l16;
-          dbl4 c[kHalves];
-#pragma unroll
-          for (int h = 0; h < kHalves; ++h) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) c[h][k] = cp[((a0 + h) * 16 + l4 + 4 * k) * LD];
-          }
-#pragma unroll
-          for (int s = 0; s < 8; ++s) {
-#pragma unroll
-            for (int h = 0; h < kHalves; ++h) c[h] = mfma_f64(-xb[((a0 + h) * 16 + l16) * kXS + 4 * s + l4], bf[s], c[h]);
-          }
-#pragma unroll
-          for (int h = 0; h < kHalves; ++h) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cp[((a0 + h) * 16 + l4 + 4 * k) * LD] = c[h][k];
-          }
-#pragma unroll
-          for (int s = 0; s < 8; ++s) bf[s] = bn[s];
-        }
-        __syncthreads();
-      }
-      if (data) {
-        // right-hand side of the block: f~_I - sum_{J<I} L(I,J) y_J, sixteen lanes per row
-        {
-          const int rr = tid >> 4, sub = tid & 15;
-          double t = 0.0;
-          for (int c = sub; c < I * kTile; c += 16) t += rb[rr * LD + c] * sy[c];
-          t = sum16(t);
-          if (sub == 0) srhs[rr] = pf[I * kTile + rr] - t;
-        }
-        __syncthreads();
-        if (wid == 0) {
-          // diagonal tile by wavefront 0: LDL^T with lane r holding row r (shifted so
-          // that element 0 is the active column), y_I on the fly, L(I,I) = U sqrt(D)
-          double B[kTile];
-          double fy = lane < kTile ? srhs[lane] : 0.0;
-#pragma unroll
-          for (int c = 0; c < kTile; ++c) B[c] = lane < kTile ? rb[lane * LD + I * kTile + c] : 0.0;
-          bool bad = false;
-          // four groups of eight pivot steps: group g reads and updates the 31 - 8 g entries
-          // that can still be live in its steps (B[1 .. 31 - j] at step j), not all 31
-          static_for<kTile / 8>([&](auto gc) {
-            constexpr int g = decltype(gc)::value;
-            constexpr int R = kTile - 1 - 8 * g;  // entries right of the group's first pivot
-            constexpr int H = R / 2;              // read before the reciprocal, so the reads overlap it
-#pragma unroll 1
-            for (int j = 8 * g; j < 8 * g + 8; ++j) {
-              // column j of the remaining rows through LDS (one wavefront: no workgroup barrier)
-              const double cj = B[0];
-              sdc[lane] = cj;
-              if (lane == j) sdy = fy;
-              wave_sync();
-              double col[R];
-#pragma unroll
-              for (int k = 0; k < H; ++k) col[k] = sdc[j + 1 + k];
-              const double d = sdc[j];
-              const double yj = sdy;
-              // 1/sqrt(d) from the hardware estimate and two Newton steps (each doubles the
-              // correct bits), then 1/d = rs^2 and sqrt(d) = d rs
-              double rs = __builtin_amdgcn_rsq(d);
-              rs = rs * (1.5 - 0.5 * d * rs * rs);
-              rs = rs * (1.5 - 0.5 * d * rs * rs);
-              const double inv = rs * rs;
-              const double t = cj * inv;
-              bad |= !(d > 0.0);
-              if (lane == j) {
-                rb[lane * LD + I * kTile + j] = d * rs;  // sqrt(d)
-                srd[j] = rs;
-                sy[I * kTile + j] = yj * rs;
-              } else if (lane > j && lane < kTile) {
-                rb[lane * LD + I * kTile + j] = cj * rs;
-              }
-              fy -= t * yj;
-#pragma unroll
-              for (int k = H; k < R; ++k) col[k] = sdc[j + 1 + k];
-#pragma unroll
-              for (int k = 0; k < R; ++k) B[k] = B[k + 1] - t * col[k];
-              wave_sync();  // every lane has read column j before it is overwritten
-            }
-          });
-          if (bad && lane == 0) s_fail = 1;
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-          // L(I,I)^-1 by forward substitution, lane k computing column k; the sums
-          // run as four independent chains and the division is by the stored 1/L_ii.
-          // Entries above the diagonal of a column are exactly zero, so the sums
-          // start at zero and the unit right-hand side enters as + 1/L_ii on the
-          // diagonal (an identity constant per row would be hoisted out of the
-          // voxel loop and spilled).
-          if (lane < kTile) {
-            double x[kTile];
-            const double* __restrict__ Ld = rb + I * kTile;
-#pragma unroll
-            for (int i = 0; i < kTile; ++i) {
-              double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#pragma unroll
-              for (int j0 = 0; j0 < i; j0 += 8) {
-                // eight entries of row i read together, then four independent chains
-                double lr[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) lr[e] = j0 + e < i ? Ld[i * LD + j0 + e] : 0.0;
-#pragma unroll
-                for (int e = 0; e < 8; e += 4) {
-                  if (j0 + e < i) s0 -= lr[e] * x[j0 + e];
-                  if (j0 + e + 1 < i) s1 -= lr[e + 1] * x[j0 + e + 1];
-                  if (j0 + e + 2 < i) s2 -= lr[e + 2] * x[j0 + e + 2];
-                  if (j0 + e + 3 < i) s3 -= lr[e + 3] * x[j0 + e + 3];
-                }
-              }
-              const double ri = srd[i];
-              x[i] = ((s0 + s1) + (s2 + s3)) * ri + (i == lane ? ri : 0.0);
-            }
-            double* __restrict__ Wi = Wt + (size_t)I * kTileDoubles;
-#pragma unroll
-            for (int i = 0; i < kTile; ++i) Wi[frag_pos(i, lane)] = x[i];
-          }
-        } else if (wid != kTileWaves / 2) {
-          // meanwhile six wavefronts (not the one sharing wavefront 0's SIMD) build columns
-          // [0, 32 I) of the next block, which no one reads any more in this block (the
-          // diagonal phase works on columns [32 I, 32 I + 32))
-          const int pc = I * kTile;
-          const int w6 = wid < kTileWaves / 2 ? wid - 1 : wid - 2;
-          const int rr = lane & (kTile - 1);
-          for (int c = 2 * w6 + lane / kTile; c < pc; c += 2 * (kTileWaves - 2)) rb[rr * LD + c] = entry(I + 1, rr, c);
-        }
-        c_pre = I * kTile;
-        __syncthreads();
-      } else {
-        // query rows of the block: variance and mean, sixteen lanes per row
-        const int rr = tid >> 4, sub = tid & 15;
-        double zz = 0.0, zy = 0.0;
-        for (int c = sub; c < nbd * kTile; c += 16) {
-          const double z = rb[rr * LD + c];
-          zz += z * z;
-          zy += z * sy[c];
-        }
-        zz = sum16(zz);
-        zy = sum16(zy);
-        const int q = (I - nbd) * kTile + rr;
-        if (sub == 0 && q < P.m) {
-          float gu, gw;
-          query_coords(P, fr, q, &gu, &gw);
-          const bool failed = s_fail != 0;
-          const double var = sf2 - zz;
-          const float vv = failed ? __int_as_float(0x7fc00000) : (float)(var > 0.0 ? var : 0.0);
-          const double fh = failed ? (double)__int_as_float(0x7fc00000) : fr.mu + zy;
-          reinterpret_cast<float4*>(io.out)[(size_t)r.v * P.m + q] = make_row(P, fr, rot, fh, gu, gw, vv);
-          if (!failed) atomicMax(&s_maxvar, __float_as_uint(vv));
-        }
-        __syncthreads();
-      }
-    }
-    if (tid == 0)
-      finish_voxel(P, io, r.v, item, r.cnt, fr.axes, s_fail != 0, false, __uint_as_float(s_maxvar), nullptr, nullptr);
-    __syncthreads();
-  }
-}
+#include "fit_strip.h"
 
 // ---------------------------------------------------------------------------
 // 2d. mixed-precision tiled solver (n up to 512): the tiled solver's block
@@ -1467,6 +1080,26 @@ __global__ void __launch_bounds__(kTileThreads) fit_tile_kernel(FitParams P, Fit
 //   block to block; with split-BF16 tile products (hi x hi + hi x lo + lo x hi)
 //   that reached 1.3e-3 s_f^2 of variance error on 200-point voxels.
 // Data tiles, diagonal inverses and L^-1 go to the workgroup's scratch area.
+constexpr int kTile = 32;
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int kTileDoubles = kTile * kTile;
+constexpr int kQTiles = 8;             // 16-query column tiles per wavefront in the query product
+constexpr int kQGroup = 16 * kQTiles;  // queries per group of the query product
+constexpr int kQTabRows = 12;          // grid rows a group of 128 queries spans (at most 11 for n_q <= 16)
+
+// Element (row, col) of a 32 x 32 tile in operand order: fragment (row half h,
+// column quad s) is 64 consecutive values, lane l holding (16 h + l % 16, 4 s + l / 16).
+__device__ __forceinline__ int frag_pos(int row, int col) {
+  return (((row >> 4) * 8 + (col >> 2)) << 6) + (row & 15) + ((col & 3) << 4);
+}
+
+// Scratch doubles per workgroup: FP32 lower tiles of L, inverses of the diagonal tiles, and the
+// lower tiles of L^-1 twice (row-major, and in matrix-core operand order).
+constexpr size_t tile_scratch_doubles_mixed(int npad) {
+  return ((size_t)(3 * ((npad / kTile) * (npad / kTile + 1) / 2) + npad / kTile) * kTileDoubles + 1) / 2;
+}
+
 typedef float flt4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ flt4 mfma_f32(float a, float b, flt4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -2046,54 +1679,76 @@ vgpr_status launch_block(vgpr_ctx* ctx, const FitParams& P, const FitArgs& io, c
   return VGPR_OK;
 }
 
-template <int NPAD, bool MIXED>
-int tile_per_cu() {
+template <int NPAD>
+int mixed_per_cu() {
   static int per_cu = -1;
-  if (per_cu < 0)
-    per_cu = MIXED ? occupancy(fit_tile_mixed_kernel<NPAD>, kTileThreads) : occupancy(fit_tile_kernel<NPAD>, kTileThreads);
+  if (per_cu < 0) per_cu = occupancy(fit_tile_mixed_kernel<NPAD>, kTileThreads);
   return per_cu;
 }
 
-int tile_per_cu_of(int b, bool mixed) {
+int mixed_per_cu_of(int b) {
   switch (kBucketCap[b]) {
-    case 64: return mixed ? tile_per_cu<64, true>() : tile_per_cu<64, false>();
-    case 96: return mixed ? tile_per_cu<96, true>() : tile_per_cu<96, false>();
-    case 128: return mixed ? tile_per_cu<128, true>() : tile_per_cu<128, false>();
-    case 256: return mixed ? tile_per_cu<256, true>() : tile_per_cu<256, false>();
-    default: return mixed ? tile_per_cu<512, true>() : tile_per_cu<512, false>();
+    case 64: return mixed_per_cu<64>();
+    case 96: return mixed_per_cu<96>();
+    case 128: return mixed_per_cu<128>();
+    case 256: return mixed_per_cu<256>();
+    default: return mixed_per_cu<512>();
   }
 }
 
-// Buckets from this one on run the tiled solvers.
+template <int NS>
+int strip_per_cu() {
+  static int per_cu = -1;
+  if (per_cu < 0) per_cu = occupancy(fit_strip_kernel<NS>, 64 * strip_waves(NS));
+  return per_cu;
+}
+
+int strip_per_cu_of(int b) {
+  switch (kBucketCap[b]) {
+    case 32: return strip_per_cu<2>();
+    case 64: return strip_per_cu<4>();
+    case 96: return strip_per_cu<6>();
+    case 128: return strip_per_cu<8>();
+    case 256: return strip_per_cu<16>();
+    default: return strip_per_cu<32>();
+  }
+}
+
+// Buckets from this one on run the mixed tiled solver in MIXED mode, and never run in float.
 int first_tile_bucket(const vgpr_ctx* ctx) { return ctx->tune.tile_first_bucket; }
 
-// Workgroups of a tiled solver for bucket b: at most one resident wave of them,
-// since each holds a scratch area.
-int tile_grid(const vgpr_ctx* ctx, int b, bool mixed, int grid_scale) {
-  const int gs = grid_scale < 4 ? grid_scale : 4;
-  const int64_t g = (int64_t)tile_per_cu_of(b, mixed) * ctx->cu_count * gs / 4;
-  return g < 1 ? 1 : (int)g;
+// Resident workgroups of bucket b's solver that holds a scratch area each. With an HBM budget the
+// 256-point strip solver keeps to one workgroup a CU, 71 MB in place of 143 MB.
+int64_t scratch_groups(const vgpr_ctx* ctx, int b, bool mixed) {
+  int per_cu = mixed ? mixed_per_cu_of(b) : strip_per_cu_of(b);
+  if (!mixed && kBucketCap[b] == 256 && ctx->budget) per_cu = 1;
+  return (int64_t)per_cu * ctx->cu_count;
 }
 
 size_t tile_bucket_bytes(const vgpr_ctx* ctx, int b, bool mixed) {
-  if (!mixed && kBucketCap[b] <= 128) return 0;  // the FP64 tiled solver keeps these tiles in LDS
-  const size_t per = mixed ? tile_scratch_doubles_mixed(kBucketCap[b]) : tile_scratch_doubles(kBucketCap[b]);
-  return (size_t)tile_per_cu_of(b, mixed) * ctx->cu_count * per * sizeof(double);
+  const size_t per = mixed ? tile_scratch_doubles_mixed(kBucketCap[b]) : strip_scratch_doubles(kBucketCap[b] / kStrip);
+  return per == 0 ? 0 : (size_t)scratch_groups(ctx, b, mixed) * per * sizeof(double);
 }
 
-template <bool MIXED>
-void launch_tile_kernel(int npad, dim3 g, dim3 t, hipStream_t s, const FitParams& P, const FitArgs& io,
-                        const Launch& l, const float4* staged, double* scratch) {
-#define VGPR_TILE_CASE(NP)                                                                                   \
-  case NP:                                                                                                   \
-    if (MIXED)                                                                                               \
-      hipLaunchKernelGGL(fit_tile_mixed_kernel<NP>, g, t, 0, s, P, io, l.recs, l.rots, staged, l.count, l.next,     \
-                         l.slots, scratch);                                                                   \
-    else                                                                                                     \
-      hipLaunchKernelGGL(fit_tile_kernel<NP>, g, t, 0, s, P, io, l.recs, l.rots, staged, l.count, l.next, l.slots,  \
-                         scratch);                                                                            \
+// Whether bucket b's solver takes a scratch area in this precision.
+bool takes_scratch(const vgpr_ctx* ctx, int b, const vgpr_params* p) {
+  const bool mixed = p->precision == VGPR_PREC_MIXED;
+  return p->max_pts > kBucketCap[b - 1] && (mixed ? b >= first_tile_bucket(ctx) : kBucketCap[b] > 128);
+}
+
+vgpr_status launch_mixed(vgpr_ctx* ctx, int b, const FitParams& P, const FitArgs& io, const float4* staged,
+                         const Launch& l, double* scratch) {
+  const int gs = l.grid_scale < 4 ? l.grid_scale : 4;  // at most one resident wave: each holds a scratch area
+  int64_t grid = scratch_groups(ctx, b, true) * gs / 4;
+  if (grid > l.max_items) grid = l.max_items;
+  if (grid < 1) grid = 1;
+  ProfScope ps(ctx, l.fam, l.stream);
+#define VGPR_TILE_CASE(NP)                                                                                       \
+  case NP:                                                                                                       \
+    hipLaunchKernelGGL(fit_tile_mixed_kernel<NP>, dim3((unsigned)grid), dim3(kTileThreads), 0, l.stream, P, io,    \
+                       l.recs, l.rots, staged, l.count, l.next, l.slots, scratch);                                 \
     break;
-  switch (npad) {
+  switch (kBucketCap[b]) {
     VGPR_TILE_CASE(64)
     VGPR_TILE_CASE(96)
     VGPR_TILE_CASE(128)
@@ -2102,47 +1757,67 @@ void launch_tile_kernel(int npad, dim3 g, dim3 t, hipStream_t s, const FitParams
     VGPR_TILE_CASE(512)
   }
 #undef VGPR_TILE_CASE
-}
-
-vgpr_status launch_tile(vgpr_ctx* ctx, int b, bool mixed, const FitParams& P, const FitArgs& io,
-                        const float4* staged, const Launch& l, double* scratch) {
-  int64_t grid = tile_grid(ctx, b, mixed, l.grid_scale);
-  if (grid > l.max_items) grid = l.max_items;
-  ProfScope ps(ctx, l.fam, l.stream);
-  if (mixed)
-    launch_tile_kernel<true>(kBucketCap[b], dim3((unsigned)grid), dim3(kTileThreads), l.stream, P, io, l, staged, scratch);
-  else
-    launch_tile_kernel<false>(kBucketCap[b], dim3((unsigned)grid), dim3(kTileThreads), l.stream, P, io, l, staged, scratch);
   VGPR_HIP(ctx, hipGetLastError());
   return VGPR_OK;
 }
 
-// One solver launch for bucket b, in precision T.
+// The strip solver over bucket b (32 points or more), FP64.
+vgpr_status launch_strip(vgpr_ctx* ctx, int b, const FitParams& P, const FitArgs& io, const float4* staged,
+                         const Launch& l, double* scratch) {
+  const bool owns = strip_scratch_doubles(kBucketCap[b] / kStrip) > 0;
+  const int gs = owns && l.grid_scale > 4 ? 4 : l.grid_scale;
+  int64_t grid = scratch_groups(ctx, b, false) * gs / 4;
+  if (grid > l.max_items) grid = l.max_items;
+  if (grid < 1) grid = 1;
+  ProfScope ps(ctx, l.fam, l.stream);
+#define VGPR_STRIP_CASE(NP)                                                                                       \
+  case NP:                                                                                                        \
+    hipLaunchKernelGGL(fit_strip_kernel<NP / kStrip>, dim3((unsigned)grid), dim3(64 * strip_waves(NP / kStrip)), 0,  \
+                       l.stream, P, io, l.recs, l.rots, staged, l.slots, l.count, l.next, scratch);                 \
+    break;
+  switch (kBucketCap[b]) {
+    VGPR_STRIP_CASE(32)
+    VGPR_STRIP_CASE(64)
+    VGPR_STRIP_CASE(96)
+    VGPR_STRIP_CASE(128)
+    VGPR_STRIP_CASE(256)
+    default:
+    VGPR_STRIP_CASE(512)
+  }
+#undef VGPR_STRIP_CASE
+  VGPR_HIP(ctx, hipGetLastError());
+  return VGPR_OK;
+}
+
+// One float solver launch for bucket b, or the 16-point bucket's double one.
 template <typename T>
 vgpr_status launch_bucket(vgpr_ctx* ctx, int b, bool wave, const FitParams& P, const FitArgs& io,
                           const float4* staged, const Launch& l) {
-  if (wave) {
-    // query rows per lane; combinations that do not fit the register file fall back to the block solver
-    const int qr = P.m <= 64 ? 1 : (P.m <= 128 ? 2 : 4);
-    if (b == 0) {
-      if (qr == 1) return launch_wave<T, 16, 1>(ctx, P, io, staged, l);
-      if (qr == 2) return launch_wave<T, 16, 2>(ctx, P, io, staged, l);
-      return launch_wave<T, 16, 4>(ctx, P, io, staged, l);
-    }
-    if (b == 1) {
-      if (qr == 1) return launch_wave<T, 32, 1>(ctx, P, io, staged, l);
-      if (qr == 2) return launch_wave<T, 32, 2>(ctx, P, io, staged, l);
-      if constexpr (sizeof(T) == 4) return launch_wave<T, 32, 4>(ctx, P, io, staged, l);
-    }
-    if (b == 2 && qr == 1) return launch_wave<T, 64, 1>(ctx, P, io, staged, l);
+  // query rows per lane; combinations that do not fit the register file fall back to the block solver
+  const int qr = P.m <= 64 ? 1 : (P.m <= 128 ? 2 : 4);
+  if (b == 0) {
+    if (!wave) return launch_block<T, 16>(ctx, P, io, staged, l);
+    if (qr == 1) return launch_wave<T, 16, 1>(ctx, P, io, staged, l);
+    if (qr == 2) return launch_wave<T, 16, 2>(ctx, P, io, staged, l);
+    return launch_wave<T, 16, 4>(ctx, P, io, staged, l);
   }
-  switch (b) {
-    case 0: return launch_block<T, 16>(ctx, P, io, staged, l);
-    case 1: return launch_block<T, 32>(ctx, P, io, staged, l);
-    case 2: return launch_block<T, 64>(ctx, P, io, staged, l);
-    case 3: return launch_block<T, 96>(ctx, P, io, staged, l);
-    default: return launch_block<T, 128>(ctx, P, io, staged, l);
+  if constexpr (sizeof(T) == 4) {
+    if (wave) {
+      if (b == 1) {
+        if (qr == 1) return launch_wave<T, 32, 1>(ctx, P, io, staged, l);
+        if (qr == 2) return launch_wave<T, 32, 2>(ctx, P, io, staged, l);
+        return launch_wave<T, 32, 4>(ctx, P, io, staged, l);
+      }
+      if (b == 2 && qr == 1) return launch_wave<T, 64, 1>(ctx, P, io, staged, l);
+    }
+    switch (b) {
+      case 1: return launch_block<T, 32>(ctx, P, io, staged, l);
+      case 2: return launch_block<T, 64>(ctx, P, io, staged, l);
+      case 3: return launch_block<T, 96>(ctx, P, io, staged, l);
+      default: return launch_block<T, 128>(ctx, P, io, staged, l);
+    }
   }
+  return fail(ctx, VGPR_E_INVALID, "no such solver");
 }
 
 // The refinement pass of the FP32 16-point wave bucket over the voxels its first pass flagged.
@@ -2159,8 +1834,8 @@ vgpr_status launch_refine(vgpr_ctx* ctx, const FitParams& P, const FitArgs& io, 
 size_t fit_work_bytes(const vgpr_ctx* ctx, int64_t n_vox, int64_t n_pts, const vgpr_params* p) {
   size_t tiles = 0;
   const bool mixed = p->precision == VGPR_PREC_MIXED;
-  for (int b = first_tile_bucket(ctx); b < kNumBuckets; ++b)
-    if (p->max_pts > kBucketCap[b - 1]) tiles += Carver::round(tile_bucket_bytes(ctx, b, mixed));
+  for (int b = 1; b < kNumBuckets; ++b)
+    if (takes_scratch(ctx, b, p)) tiles += Carver::round(tile_bucket_bytes(ctx, b, mixed));
   const size_t rot_bytes = p->frame_mode == 1 ? Carver::round(sizeof(RotRec) * (size_t)n_vox * kNumBuckets) : 0;
   return rot_bytes + Carver::round(sizeof(SlotRec) * (size_t)n_vox * kNumBuckets) + Carver::round(sizeof(float4) * (size_t)n_pts) +
          Carver::round(sizeof(int32_t) * (size_t)n_vox) + Carver::round(sizeof(int4) * (size_t)n_vox) +
@@ -2195,9 +1870,8 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   uint32_t* ctr = cv.take<uint32_t>(64);
   double* tile_scratch[kNumBuckets] = {};
   const bool mixed = p->precision == VGPR_PREC_MIXED;
-  for (int b = first_tile_bucket(ctx); b < kNumBuckets; ++b)
-    if (p->max_pts > kBucketCap[b - 1])
-      tile_scratch[b] = cv.take<double>(tile_bucket_bytes(ctx, b, mixed) / sizeof(double));
+  for (int b = 1; b < kNumBuckets; ++b)
+    if (takes_scratch(ctx, b, p)) tile_scratch[b] = cv.take<double>(tile_bucket_bytes(ctx, b, mixed) / sizeof(double));
   hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, ctx->stream, ctr, 64);
 
   // the wave solver holds up to four query rows per lane (grids up to 256 points) for voxels of up
@@ -2252,17 +1926,19 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
     return s == 0 ? ctx->stream : ctx->aux[s - 1];
   };
   bool merge_top = false;  // set below, once the launched buckets are known
+  auto runs_fp32 = [&](int b) { return fp32 && b <= tu.fp32_last_bucket && b < first_tile_bucket(ctx); };
+  // buckets taken longest voxel first: above 64 points one voxel is long enough to be left over at the end
+  auto ordered = [&](int b) { return b >= 3 ? !runs_fp32(b) : b >= first_tile_bucket(ctx); };
   auto launch_b = [&](int b) -> vgpr_status {
     const bool tiled = b >= first_tile_bucket(ctx);
     const bool wave = wave_ok(b) && b <= tu.wave_last_bucket;
-    const bool in_fp32 = fp32 && b <= tu.fp32_last_bucket && !tiled;
+    const bool in_fp32 = runs_fp32(b);
     FitParams Pb = P;
     Pb.mode = in_fp32 ? 0 : 2;
     const RotRec* rb_ = rots ? rots + (size_t)b * a.n_vox : nullptr;
     Launch l{stream_of(b), tu.grid_scale[b], recs + (size_t)b * a.n_vox, rb_, nullptr, ctr + b, ctr + 8 + b,
              rlists + (size_t)b * a.n_vox, ctr + 16 + b, a.n_vox, kFam[in_fp32 ? 0 : 2][b]};
-    if (tiled) {
-      if (mixed) l.fam = kFamMixed[b];
+    if (ordered(b)) {
       // largest voxels first: the bucket's (otherwise unused) re-solve list holds the order,
       // sorted before the fork
       if (b == kNumBuckets - 1 && merge_top) {
@@ -2273,8 +1949,12 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
         l.count = ctr + 49;
       }
       l.slots = rlists + (size_t)b * a.n_vox;
-      return launch_tile(ctx, b, mixed, Pb, a, staged, l, tile_scratch[b]);
     }
+    if (tiled && mixed) {
+      l.fam = kFamMixed[b];
+      return launch_mixed(ctx, b, Pb, a, staged, l, tile_scratch[b]);
+    }
+    if (!in_fp32 && b > 0) return launch_strip(ctx, b, Pb, a, staged, l, tile_scratch[b]);
     const bool refine_pass = in_fp32 && wave && b == 0;  // the wave shape that hands voxels to the refinement pass
     if (refine_pass) {
       l.flist = flists + (size_t)b * a.n_vox;
@@ -2296,7 +1976,8 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
     R.mode = 1;
     Launch lr{stream_of(b), tu.grid_scale[b], recs + (size_t)b * a.n_vox, rb_, rlists + (size_t)b * a.n_vox,
               ctr + 16 + b, ctr + 24 + b, nullptr, nullptr, a.n_vox, kFam[1][b]};
-    return launch_bucket<double>(ctx, b, wave, R, a, staged, lr);
+    return b > 0 ? launch_strip(ctx, b, R, a, staged, lr, tile_scratch[b])
+                 : launch_bucket<double>(ctx, b, wave, R, a, staged, lr);
   };
   auto launched = [&](int b) { return p->max_pts > (b ? P.bcap[b - 1] : 0); };
   // 256- and 512-point buckets merged into the 512-point launch (the combined slots must fit int32)
@@ -2307,8 +1988,8 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
     // longest-first orders of the tiled buckets, one workgroup each
     OrderJobs oj{};
     int nj = 0;
-    for (int b = first_tile_bucket(ctx); b < kNumBuckets; ++b) {
-      if (!launched(b) || skipped(b)) continue;
+    for (int b = 1; b < kNumBuckets; ++b) {
+      if (!launched(b) || skipped(b) || !ordered(b)) continue;
       const bool merged = b == kNumBuckets - 1 && merge_top;
       OrderJob& j = oj.job[nj++];
       j.recs = recs + (size_t)(merged ? b - 1 : b) * a.n_vox;
