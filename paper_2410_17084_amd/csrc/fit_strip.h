@@ -93,10 +93,19 @@ using TilePtr = __attribute__((address_space(AS))) char*;
 constexpr int kAsGlobal = 1, kAsLds = 3;
 constexpr int kTileBytes = kTileDbl * 8;
 
+// A base address kept in scalar registers: the tile's offset is added there and the lane's offset in the
+// access, so that no vector register holds an address (136 of them would be computed ahead of the voxel loop).
+template <int AS>
+__device__ __forceinline__ TilePtr<AS> tile_at(TilePtr<AS> T, int index) {
+  if constexpr (AS == kAsGlobal) index = __builtin_amdgcn_readfirstlane(index);
+  TilePtr<AS> p = T + (size_t)(uint32_t)index * kTileBytes;
+  if constexpr (AS == kAsGlobal) asm volatile("" : "+s"(p));
+  return p;
+}
 template <int AS>
 __device__ __forceinline__ Tile tile_load(TilePtr<AS> T, int index, uint32_t off) {
   typedef const __attribute__((address_space(AS))) dbl2* Half;
-  const TilePtr<AS> p = T + (size_t)index * kTileBytes;
+  const TilePtr<AS> p = tile_at<AS>(T, index);
   Tile t;
   t.h[0] = *(Half)(p + off);
   t.h[1] = *(Half)(p + kTileBytes / 2 + off);
@@ -105,13 +114,13 @@ __device__ __forceinline__ Tile tile_load(TilePtr<AS> T, int index, uint32_t off
 template <int AS>
 __device__ __forceinline__ void tile_store(TilePtr<AS> T, int index, uint32_t off, dbl4 v) {
   typedef __attribute__((address_space(AS))) dbl2* Half;
-  const TilePtr<AS> p = T + (size_t)index * kTileBytes;
+  const TilePtr<AS> p = tile_at<AS>(T, index);
   *(Half)(p + off) = dbl2{v[0], v[1]};
   *(Half)(p + kTileBytes / 2 + off) = dbl2{v[2], v[3]};
 }
 
 // A value the compiler takes as new at every use: what is computed from it is computed where it is used,
-// instead of being kept in a register from before the voxel loop (136 tile addresses, 32 loop bounds).
+// instead of being kept in a register from before the voxel loop.
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -125,11 +134,16 @@ __device__ __forceinline__ double uniform(double v) {
   return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                           __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
-template <int AS>
-__device__ __forceinline__ TilePtr<AS> fresh_base(TilePtr<AS> p) {
-  if constexpr (AS == kAsGlobal) asm volatile("" : "+s"(p));
-  return p;
+// The value of the lane whose number differs in the bits of `mask`.
+__device__ __forceinline__ double from_lane_xor(double v, int mask, int lane) {
+  const int at = (fresh(lane) ^ mask) << 2;
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(at, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(at, __double2loint(v)));
 }
+
+// Keeps the fetches issued before it before it: the compiler would sink a fetch into the branch that uses its
+// value, to wait there for all of its latency.
+__device__ __forceinline__ void issued() { asm volatile("" ::: "memory"); }
 
 // First tile (the diagonal one) of column j: tiles (j .. NS - 1, j) follow one another.
 template <int NS>
@@ -156,7 +170,9 @@ __device__ __forceinline__ void update_column(dbl4 (&acc)[NS], TilePtr<AS> T, in
       Ahead<D> n;
 #pragma unroll
       for (int e = 0; e + 1 < D; ++e) n.t[e] = q.t[e + 1];
-      if constexpr (i + D < NS) n.t[D - 1] = tile_load<AS>(T, tile_col<NS>(J) + 1 + K + D, off);
+      // past the column's end the last tile again: a fetch of anything else would be waited for in its turn
+      if constexpr (i + D < NS) n.t[D - 1] = tile_load<AS>(T, tile_col<NS>(J) + min(1 + K + D, rows - 1 - J), off);
+      issued();
       if constexpr (J == 0) acc[i] = init(i);
 #pragma unroll
       for (int s = 0; s < 4; ++s) acc[i] = mfma_f64(t[s], z[s], acc[i]);
@@ -165,51 +181,49 @@ __device__ __forceinline__ void update_column(dbl4 (&acc)[NS], TilePtr<AS> T, in
   }
 }
 
-// The first D tiles of column J.
-template <int NS, int D, int J, int AS>
-__device__ __forceinline__ Ahead<D> column_head(TilePtr<AS> T, uint32_t off) {
-  Ahead<D> n;
+// Tiles FROM .. TO - 1 of column J's window (column J has rows - J tiles, its diagonal one among them).
+template <int NS, int FROM, int TO, int J, int AS, int D>
+__device__ __forceinline__ void column_head(TilePtr<AS> T, int rows, uint32_t off, Ahead<D>& n) {
 #pragma unroll
-  for (int e = 0; e < D; ++e)
-    if (J + 1 + e < NS) n.t[e] = tile_load<AS>(T, tile_col<NS>(J) + 1 + e, off);
-  return n;
+  for (int e = FROM; e < TO; ++e)
+    if (J + 1 + e < NS) n.t[e] = tile_load<AS>(T, tile_col<NS>(J) + max(min(1 + e, rows - 1 - J), 0), off);
 }
 
-template <int NS, int D, bool EARLY, int J, int AS, typename I, typename F>
+template <int NS, int D, int H, int J, int AS, typename I, typename F>
 __device__ __forceinline__ void eliminate_from(dbl4 (&acc)[NS], TilePtr<AS> T, int rows_, uint32_t off, Tile w, Ahead<D> q,
                                                I&& init, F&& step) {
   if constexpr (J < NS) {
     const int rows = fresh_uniform(rows_);
     if (J < rows) {
-      const TilePtr<AS> Tj = fresh_base<AS>(T);
-      if constexpr (!EARLY) q = column_head<NS, D, J, AS>(Tj, off);
+      column_head<NS, H, D, J, AS>(T, rows, off, q);
+      issued();
       dbl4 z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int s = 0; s < 4; ++s) z = mfma_f64(w[s], acc[J][s], z);
       Tile wn{};
       Ahead<D> n;
-      if constexpr (J + 1 < NS) wn = tile_load<AS>(Tj, tile_col<NS>(J + 1), off);
-      if constexpr (EARLY) n = column_head<NS, D, J + 1, AS>(Tj, off);
+      if constexpr (J + 1 < NS) wn = tile_load<AS>(T, J + 1 < rows ? tile_col<NS>(J + 1) : tile_col<NS>(J), off);
+      column_head<NS, 0, H, J + 1, AS>(T, rows, off, n);
+      issued();
       step(J, z);
-      update_column<NS, D, J, 0, AS>(acc, Tj, rows, off, z, q, init);
-      eliminate_from<NS, D, EARLY, J + 1, AS>(acc, T, rows_, off, wn, n, init, step);
+      update_column<NS, D, J, 0, AS>(acc, T, rows, off, z, q, init);
+      eliminate_from<NS, D, H, J + 1, AS>(acc, T, rows_, off, wn, n, init, step);
     }
   }
 }
 
 // Eliminate `rows` strips (at least one) of sixteen columns whose kernel tiles are init(i), taken when column 0
 // reaches them: Z(j) goes to step(j, Z). Tiles are stored negated, so that an update adds; they are fetched D
-// ahead, the inverse of the next diagonal tile while a column runs, and a column's first D tiles while the one
-// before runs (EARLY) or while its Z is formed. Tiles of strips past `rows` may be fetched; nothing of them is
-// used.
-template <int NS, int D, bool EARLY, int AS, typename I, typename F>
+// ahead: the inverse of the next diagonal tile and a column's first H tiles while the column before runs, the
+// rest of its first D while its Z is formed.
+template <int NS, int D, int H, int AS, typename I, typename F>
 __device__ __forceinline__ void eliminate(TilePtr<AS> T, int rows, uint32_t off, I&& init, F&& step) {
   dbl4 acc[NS];
   Ahead<D> q;
   const Tile w = tile_load<AS>(T, 0, off);
-  if constexpr (EARLY) q = column_head<NS, D, 0, AS>(T, off);
+  column_head<NS, 0, H, 0, AS>(T, rows, off, q);
   acc[0] = init(0);
-  eliminate_from<NS, D, EARLY, 0, AS>(acc, T, rows, off, w, q, init, step);
+  eliminate_from<NS, D, H, 0, AS>(acc, T, rows, off, w, q, init, step);
 }
 
 // cor[t] -= L(i0 + t, j) L(r, j)^T for t < C over the eliminated strips j < i0: the tiles are stored negated,
@@ -252,12 +266,16 @@ __device__ __forceinline__ bool factor16(dbl4 D, int lane_, double (&W)[4]) {
   bool ok = true;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    double p[4], f[4];
+    double p[4], f[4];  // entries 4 b + c of row l16 of the tile and of F, on their way while the pivots are found
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      p[c] = __shfl(D[b], c * 16 + l16, 64);
-      f[c] = __shfl(F[b], c * 16 + l16, 64);
+      const int at = (c * 16 + l16) << 2;
+      p[c] = __hiloint2double(__builtin_amdgcn_ds_bpermute(at, __double2hiint(D[b])),
+                              __builtin_amdgcn_ds_bpermute(at, __double2loint(D[b])));
+      f[c] = __hiloint2double(__builtin_amdgcn_ds_bpermute(at, __double2hiint(F[b])),
+                              __builtin_amdgcn_ds_bpermute(at, __double2loint(F[b])));
     }
+    issued();
     auto d = [&](int r, int c) { return bcast(D[b], r * 16 + 4 * b + c); };
     const double d0 = d(0, 0), r0 = rsqrt_step(d0);
     const double l10 = d(1, 0) * r0, l20 = d(2, 0) * r0, l30 = d(3, 0) * r0;
@@ -267,28 +285,32 @@ __device__ __forceinline__ bool factor16(dbl4 D, int lane_, double (&W)[4]) {
     const double l32 = fma(-l31, l21, fma(-l30, l20, d(3, 2))) * r2;
     const double d3 = fma(-l32, l32, fma(-l31, l31, fma(-l30, l30, d(3, 3)))), r3 = rsqrt_step(d3);
     ok = ok && d0 > 0.0 && d1 > 0.0 && d2 > 0.0 && d3 > 0.0;
-    auto solve = [&](const double (&v)[4]) {
-      double x0 = v[0] * r0;
-      double x1 = fma(-x0, l10, v[1]) * r1;
-      double x2 = fma(-x1, l21, fma(-x0, l20, v[2])) * r2;
-      double x3 = fma(-x2, l32, fma(-x1, l31, fma(-x0, l30, v[3]))) * r3;
-      // all four on every lane: the chain must not be split into branches by l / 16
-      asm volatile("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
-      const double lo = l4 & 1 ? x1 : x0, hi = l4 & 1 ? x3 : x2;
-      return l4 & 2 ? hi : lo;
-    };
-    const double y = solve(f);
+    // both rows together; all four entries on every lane (the chain must not be split into branches by l / 16)
+    double x0 = p[0] * r0, y0 = f[0] * r0;
+    double x1 = fma(-x0, l10, p[1]) * r1, y1 = fma(-y0, l10, f[1]) * r1;
+    double x2 = fma(-x1, l21, fma(-x0, l20, p[2])) * r2, y2 = fma(-y1, l21, fma(-y0, l20, f[2])) * r2;
+    double x3 = fma(-x2, l32, fma(-x1, l31, fma(-x0, l30, p[3]))) * r3;
+    double y3 = fma(-y2, l32, fma(-y1, l31, fma(-y0, l30, f[3]))) * r3;
+    asm volatile("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3));
+    const double ylo = l4 & 1 ? y1 : y0, yhi = l4 & 1 ? y3 : y2, y = l4 & 2 ? yhi : ylo;
     W[b] = y;
     if (b < 3) {
+      const double xlo = l4 & 1 ? x1 : x0, xhi = l4 & 1 ? x3 : x2;
       // rows above the panel's diagonal are finished (their entries are rounding residue)
-      const double xs = solve(p);
-      const double x = l16 >= 4 * b + l4 ? xs : 0.0;
+      const double x = l16 >= 4 * b + l4 ? (l4 & 2 ? xhi : xlo) : 0.0;
       D = mfma_f64(x, -x, D);
       F = mfma_f64(x, -y, F);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
   return ok;
+}
+
+// Workgroup barrier that orders LDS only: global stores may still be on their way.
+__device__ __forceinline__ void sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 template <int NS>
@@ -301,14 +323,16 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
   constexpr int N = NS * kStrip;
   constexpr bool kLds = strip_lds(NS);
   constexpr bool kTab = !kLds;              // separable query tables in LDS
-  constexpr int D = NS >= 32 ? 4 : (NS == 16 || NS == 2 ? 1 : 2);  // tiles in flight
+  constexpr int D = NS >= 32 ? 4 : (NS == 2 ? 1 : 2);  // tiles in flight
+  constexpr int kBatch = NS <= 8 ? 4 : 1;                          // rounds of queries written together
+  constexpr int H = NS >= 32 ? 4 : 0;                              // ... of the next column
   constexpr int TS = N + 4;                 // row stride of the query tables (16 rows 4 apart: no bank conflict)
   constexpr int kPub = kTab ? 4 * kTileDbl : 2;
   constexpr int kBig = kLds ? strip_tiles(NS) * kTileDbl : (2 * kMaxGridSide * TS > kPub ? 2 * kMaxGridSide * TS : kPub);
   __shared__ __attribute__((aligned(16))) double s_big[kBig];  // the tiles, or the query tables (data phase: pub)
   __shared__ double pu[N], pw[N], pf[N], sy[N];
   __shared__ float pn[N];
-  __shared__ double s_frac[kMaxGridSide];
+  __shared__ double s_frac[kMaxGridSide], gridu[kMaxGridSide], gridw[kMaxGridSide];
   __shared__ int s_item, s_fail;
   __shared__ unsigned s_maxvar;
 
@@ -342,17 +366,21 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
     const RotRec* rot = rots ? rots + slot : nullptr;
     const int n = fr.n;
     const int nb = (n + kStrip - 1) / kStrip;
-    // the next voxel's number is on its way while this one is solved
-    uint32_t ahead = 0;
     if (tid == 0) {
-      ahead = gridDim.x + atomicAdd(fetch, 1u);
       s_fail = 0;
       s_maxvar = 0u;
     }
     // coordinates scaled so that kappa = s_f^2 2^-(du^2 + dw^2); the padding points lie so far from the
     // data, the queries and each other that their kernel entries are zero
-    const double sc = uniform(sqrt(fr.lam * 1.4426950408889634));
-    for (int i = tid; i < nb * kStrip; i += NT) {
+    const double lam2 = fr.lam * 1.4426950408889634;
+    const double sc = uniform(lam2 * rsqrt_step(lam2));
+    if (const int i = fresh(tid); i < P.nq) {
+      float gu, gw;
+      coords_from_frac(P, fr, s_frac[i], s_frac[i], &gu, &gw);
+      gridu[i] = ((double)gu - fr.anc_u) * sc;
+      gridw[i] = ((double)gw - fr.anc_w) * sc;
+    }
+    for (int i = fresh(tid); i < nb * kStrip; i += NT) {
       double xu = 1e30 * (i + 1), xw = 0.0, fv = 0.0;
       float nz = 0.f;
       if (i < n) {
@@ -384,20 +412,23 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
     const int njobs = (nb + WV - 1) / WV;                     // rounds of WV data strips
     const int nqueries = (P.m + WV * kStrip - 1) / (WV * kStrip);  // rounds of WV x 16 queries
     float maxvar = 0.f;
+    double qzz = 0.0, qzy = 0.0;  // up to four rounds' sums of this lane's query
+    uint32_t ahead = 0;
 #pragma unroll 1
     for (int job = 0; job < njobs + nqueries; ++job) {
       const bool data = job < njobs;
       if (job == njobs) {
+        // the next voxel's number is fetched while the queries run: by now the workgroups are apart (all of
+        // them asking as they start waited up to 40 us on the one counter)
+        if (tid == 0) ahead = items > (int)gridDim.x ? gridDim.x + atomicAdd(fetch, 1u) : (uint32_t)items;
         sync();  // the factor is complete
         if constexpr (kTab) {
           // kappa factors over the grid's rows and columns: two tables of n_q x n entries
           double* tu = s_big;
           double* tw = s_big + kMaxGridSide * TS;
           for (int i = 0; i < P.nq; ++i) {
-            float gu, gw;
-            coords_from_frac(P, fr, s_frac[i], s_frac[i], &gu, &gw);
-            const double qu = ((double)gu - fr.anc_u) * sc, qw = ((double)gw - fr.anc_w) * sc;
-            for (int c = tid; c < nb * kStrip; c += NT) {
+            const double qu = gridu[i], qw = gridw[i];
+            for (int c = fresh(tid); c < nb * kStrip; c += NT) {
               const double du = qu - pu[c], dw = qw - pw[c];
               tu[i * TS + c] = sf2 * exp2_neg(-(du * du));
               tw[i * TS + c] = exp2_neg(-(dw * dw));
@@ -414,7 +445,6 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
       dbl4 own = {0.0, 0.0, 0.0, 0.0};     // data: K + S of the strip with itself, minus the eliminated strips
       dbl4 cor[WV > 1 ? WV - 1 : 1];       // data: ... and of the round's earlier strips with it
       double zy = 0.0, zz = 0.0;           // sums of Z y and Z^2 over this lane's rows
-      float gu = 0.f, gw = 0.f;
       if (active) {
         const int l16 = fresh(lane) & 15;
         double xu, xw;
@@ -437,9 +467,8 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         } else {
           const int q = q0 + l16 < P.m ? q0 + l16 : P.m - 1;
           const int qi = q / P.nq, qj = q - qi * P.nq;
-          coords_from_frac(P, fr, s_frac[qi], s_frac[qj], &gu, &gw);
-          xu = ((double)gu - fr.anc_u) * sc;
-          xw = ((double)gw - fr.anc_w) * sc;
+          xu = gridu[qi];
+          xw = gridw[qj];
           if constexpr (kTab) {
             tu = s_big + qi * TS + (fresh(lane) >> 4);
             tw = s_big + (kMaxGridSide + qj) * TS + (fresh(lane) >> 4);
@@ -447,7 +476,7 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         }
         if (rows > 0) {
           const double* ys = sy + (fresh(lane) >> 4);
-          eliminate<NS, D, (NS >= 32), AS>(
+          eliminate<NS, D, H, AS>(
               T, rows, off,
               [&](int i) {
                 if constexpr (kTab) {
@@ -481,6 +510,9 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         }
         if constexpr (WV > 1) {
           if (data) {
+            const int at = r * kStrip + (fresh(lane) & 15);  // read again: two values less to hold until here
+            xu = pu[at];
+            xw = pw[at];
 #pragma unroll
             for (int t = 0; t < WV - 1; ++t)
               if (t < w) cor[t] = kernel_tile(i0 + t, xu, xw);
@@ -488,17 +520,28 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         }
       }
       if (!data) {
-        if (active) {
-          zz += __shfl_xor(zz, 16, 64);
-          zy += __shfl_xor(zy, 16, 64);
-          zz += __shfl_xor(zz, 32, 64);
-          zy += __shfl_xor(zy, 32, 64);
-          const int q = q0 + (fresh(lane) & 15);
-          if (lane < kStrip && q < P.m) {
+        // the round's 16 queries: their sums over the rows go to the lanes with l / 16 = round % kBatch, so that
+        // kBatch rounds are written together, one query a lane
+        const int round = job - njobs;
+        zz += from_lane_xor(zz, 16, lane);
+        zy += from_lane_xor(zy, 16, lane);
+        zz += from_lane_xor(zz, 32, lane);
+        zy += from_lane_xor(zy, 32, lane);
+        const int l4 = fresh(lane) >> 4, at = round & (kBatch - 1);
+        if (kBatch == 1 || l4 == at) {
+          qzz = zz;
+          qzy = zy;
+        }
+        if (at == kBatch - 1 || round + 1 == nqueries) {
+          const int q = ((round - at + l4) * WV + w) * kStrip + (fresh(lane) & 15);
+          if (l4 <= at && q < P.m) {
+            const int qi = q / P.nq, qj = q - qi * P.nq;
+            float gu, gw;
+            coords_from_frac(P, fr, s_frac[qi], s_frac[qj], &gu, &gw);
             const bool failed = s_fail != 0;
-            const double var = sf2 - zz;
+            const double var = sf2 - qzz;
             const float vv = failed ? __int_as_float(0x7fc00000) : (float)(var > 0.0 ? var : 0.0);
-            const double fh = failed ? (double)__int_as_float(0x7fc00000) : fr.mu + zy;
+            const double fh = failed ? (double)__int_as_float(0x7fc00000) : fr.mu + qzy;
             reinterpret_cast<float4*>(io.out)[(size_t)rec.v * P.m + q] = make_row(P, fr, rot, fh, gu, gw, vv);
             maxvar = fmaxf(maxvar, failed ? 0.f : vv);
           }
@@ -526,8 +569,8 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
           if (!ok) s_fail = 1;
           const int l16 = fresh(lane) & 15, l4 = fresh(lane) >> 4;
           // the right-hand side's rows, then y = W rhs
-          zy += __shfl_xor(zy, 16, 64);
-          zy += __shfl_xor(zy, 32, 64);
+          zy += from_lane_xor(zy, 16, lane);
+          zy += from_lane_xor(zy, 32, lane);
           const double g = pf[it * kStrip + l16] - zy;
           // element (4 b + l / 16, l % 16) of W goes where a left operand's lanes read it
           const int at = (l16 >> 3) * 128 + ((l16 & 3) * 16 + l4) * 2 + ((l16 >> 2) & 1);
@@ -543,8 +586,10 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         }
         if constexpr (WV > 1) {
           if (it + 1 >= nb) break;  // no later strip (the same for every wavefront)
-          sync();
-          if (t + 1 < WV) {
+          if (t + 1 == WV) {
+            sync();  // the next round reads this one's tiles
+          } else {
+            sync_lds();
             dbl4 z = {0.0, 0.0, 0.0, 0.0};
             if (w > t && active) {
               const Tile wt = kTab ? tile_load<kAsLds>(pub, 0, off) : tile_load<AS>(T, tile_col<NS>(it), off);
@@ -562,7 +607,7 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
                 own = mfma_f64(z[k], m[k], own);
               }
             }
-            sync();
+            sync_lds();
             if (active) {
 #pragma unroll
               for (int t2 = t + 1; t2 < WV - 1; ++t2)
@@ -579,7 +624,7 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
       if constexpr (WV == 1) sync();
     }
 #pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) maxvar = fmaxf(maxvar, __shfl_xor(maxvar, d, 64));
+    for (int d = 32; d >= 1; d >>= 1) maxvar = fmaxf(maxvar, __shfl_xor(maxvar, d, 64));
     if (lane == 0) atomicMax(&s_maxvar, __float_as_uint(maxvar));
     if (tid == 0) s_item = (int)ahead;
     sync();
