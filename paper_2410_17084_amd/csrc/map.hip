@@ -81,87 +81,97 @@ __global__ void __launch_bounds__(256) probe_kernel(const uint64_t* __restrict__
   if (lane_id() == 0 && m) atomicAdd(&counters[1], (unsigned long long)__popcll(m));
 }
 
-// One wave per frame voxel: insert or find, append points, flag for solving.
+// Insert or find the frame's voxels, append their points, flag those to solve. A workgroup takes 64 voxels: its
+// first wavefront looks them up, one a lane, and numbers the new ones with a single counter update for all of them
+// (one update a voxel on that counter took 105 us for the 12k voxels of a 45k-point frame, and all of a new map's
+// frames wait for it); then 16 lanes a voxel copy the points, since a frame brings a voxel only a few.
+constexpr int kInsertVoxels = 64;
+constexpr int kInsertLanes = 16;  // lanes that copy one voxel's points
 __global__ void __launch_bounds__(256) insert_kernel(vgpr_map M, const float* __restrict__ xyz,
                                                      const uint64_t* __restrict__ keys,
                                                      const int32_t* __restrict__ offs, const int32_t* __restrict__ cnts,
                                                      const int32_t* __restrict__ perm, int64_t nv, int cap, int tau,
                                                      uint32_t* __restrict__ flag, int32_t* __restrict__ ids) {
-  const int64_t v = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  const int lane = lane_id();
-  if (v >= nv) return;
-  const uint64_t key = keys[v];
-  int id = -1;
-  int stored = 0;
-  int inmap = 0;
-  if (lane == 0) {
-    int64_t s = (int64_t)(mix64(key) & (uint64_t)(M.nslots - 1));
-    for (int64_t probe = 0; probe < M.nslots; ++probe) {
-      const unsigned long long prev =
-          atomicCAS(reinterpret_cast<unsigned long long*>(&M.slot_key[s]), (unsigned long long)kKeySentinel,
-                    (unsigned long long)key);
-      if (prev == kKeySentinel) {
-        // new voxel: keys are unique within a frame, so no other lane races on it
-        id = (int)atomicAdd(&M.counters[0], 1ull);
-        if (id >= M.max_voxels) {  // the host checks capacity first; never index past the records
-          M.slot_id[s] = -1;
-          id = -1;
+  __shared__ int s_id[kInsertVoxels], s_at[kInsertVoxels], s_take[kInsertVoxels], s_off[kInsertVoxels];
+  const int64_t v0 = (int64_t)blockIdx.x * kInsertVoxels;
+  if (threadIdx.x < kInsertVoxels) {
+    const int lane = lane_id();
+    const int64_t v = v0 + lane;
+    const bool valid = v < nv;
+    const uint64_t key = valid ? keys[v] : 0;
+    int64_t s = -1;
+    bool is_new = false;
+    if (valid) {
+      int64_t at = (int64_t)(mix64(key) & (uint64_t)(M.nslots - 1));
+      for (int64_t probe = 0; probe < M.nslots; ++probe) {
+        const unsigned long long prev =
+            atomicCAS(reinterpret_cast<unsigned long long*>(&M.slot_key[at]), (unsigned long long)kKeySentinel,
+                      (unsigned long long)key);
+        if (prev == kKeySentinel || prev == key) {
+          // keys are unique within a frame, so no other lane races on a new one
+          is_new = prev == kKeySentinel;
+          s = at;
           break;
         }
-        M.slot_id[s] = id;
+        at = (at + 1) & (M.nslots - 1);
+      }
+    }
+    const unsigned long long news = __ballot(is_new);
+    unsigned long long first = 0;
+    if (lane == 0 && news) first = atomicAdd(&M.counters[0], (unsigned long long)__popcll(news));
+    first = __shfl(first, 0, 64);
+    int id = -1, stored = 0, inmap = 0, total = 0;
+    bool conv = false;
+    if (is_new) {
+      const unsigned long long k = first + (unsigned long long)__popcll(news & ((1ull << lane) - 1ull));
+      // the host checks capacity first; never index past the records
+      id = k < (unsigned long long)M.max_voxels ? (int)k : -1;
+      M.slot_id[s] = id;
+      if (id >= 0) {
         M.vkey[id] = key;
-        M.vstored[id] = 0;
-        M.vtotal[id] = 0;
         M.vconv[id] = 0;
         if (M.vpred) M.vpred[id] = 0;
-        break;
       }
-      if (prev == key) {
-        id = M.slot_id[s];
-        if (id >= 0) {
-          stored = M.vstored[id];
-          inmap = M.vpred ? M.vpred[id] : 0;
-        }
-        break;
+    } else if (s >= 0) {
+      id = M.slot_id[s];
+      if (id >= 0) {
+        stored = M.vstored[id];
+        total = M.vtotal[id];
+        conv = M.vconv[id] != 0;
+        inmap = M.vpred ? M.vpred[id] : 0;
       }
-      s = (s + 1) & (M.nslots - 1);
     }
-  }
-  // the record is read and written by lane 0 only; other lanes get it by shuffle
-  id = __shfl(id, 0, 64);
-  stored = __shfl(stored, 0, 64);
-  inmap = __shfl(inmap, 0, 64);
-  if (id < 0) {
-    if (lane == 0) {
-      flag[v] = 0u;
-      ids[v] = 0;
+    int take = 0;
+    if (valid) {
+      uint32_t fl = 0u;
+      if (id >= 0) {
+        const int c = cnts[v];
+        // feedback map, voxel already solved: its new points go to the re-solve, not the pool
+        take = inmap ? 0 : max(0, min(c, cap - stored));
+        const int now = stored + take;
+        M.vtotal[id] = total + c;
+        if (!inmap) M.vstored[id] = now;
+        fl = (inmap || now >= tau) && !conv ? 1u : 0u;
+      }
+      flag[v] = fl;
+      ids[v] = id >= 0 ? id : 0;
     }
-    return;
+    s_id[lane] = id;
+    s_at[lane] = stored;
+    s_take[lane] = take;
+    s_off[lane] = take > 0 ? offs[v] : 0;
   }
-  const int c = cnts[v];
-  if (inmap) {  // feedback map, voxel already solved: its new points go to the re-solve, not the pool
-    if (lane == 0) {
-      M.vtotal[id] += c;
-      ids[v] = id;
-      flag[v] = M.vconv[id] ? 0u : 1u;
+  __syncthreads();
+  const int sub = threadIdx.x & (kInsertLanes - 1);
+  for (int u = threadIdx.x / kInsertLanes; u < kInsertVoxels; u += 256 / kInsertLanes) {
+    const int take = s_take[u];
+    for (int i = sub; i < take; i += kInsertLanes) {
+      const int src = perm[s_off[u] + i];
+      float* dst = M.pool + ((size_t)s_id[u] * cap + s_at[u] + i) * 3;
+      dst[0] = xyz[3 * (size_t)src + 0];
+      dst[1] = xyz[3 * (size_t)src + 1];
+      dst[2] = xyz[3 * (size_t)src + 2];
     }
-    return;
-  }
-  const int take = min(c, cap - stored);
-  const int o = offs[v];
-  for (int i = lane; i < take; i += 64) {
-    const int src = perm[o + i];
-    float* dst = M.pool + ((size_t)id * cap + stored + i) * 3;
-    dst[0] = xyz[3 * (size_t)src + 0];
-    dst[1] = xyz[3 * (size_t)src + 1];
-    dst[2] = xyz[3 * (size_t)src + 2];
-  }
-  if (lane == 0) {
-    const int now = stored + (take > 0 ? take : 0);
-    M.vstored[id] = now;
-    M.vtotal[id] += c;
-    ids[v] = id;
-    flag[v] = (now >= tau && !M.vconv[id]) ? 1u : 0u;
   }
 }
 
@@ -588,7 +598,7 @@ vgpr_status vgpr_map_update(vgpr_map* M, const float* d_xyz, int64_t n_pts, uint
   }
 
   const int64_t nvb = (nv + kCompactTile - 1) / kCompactTile;
-  hipLaunchKernelGGL(insert_kernel, dim3((unsigned)((nv + 3) / 4)), dim3(256), 0, ctx->stream, *M, d_xyz, fkeys,
+  hipLaunchKernelGGL(insert_kernel, dim3((unsigned)((nv + kInsertVoxels - 1) / kInsertVoxels)), dim3(256), 0, ctx->stream, *M, d_xyz, fkeys,
                      foff, fcnt, fperm, nv, p.max_pts, p.min_pts, flag, ids);
   hipLaunchKernelGGL(compact_reduce, dim3((unsigned)nvb), dim3(1024), 0, ctx->stream, *M, flag, ids, nv, bsum, bpts);
   hipLaunchKernelGGL(compact_scan, dim3(1), dim3(1024), 0, ctx->stream, bsum, bpts, (int)nvb, dtot);
