@@ -1,20 +1,34 @@
 // vgpr_voxelize: the STORE step of Alg. S1 (paper supplementary) on the GPU.
 //
-// 1. key kernel: one thread per point computes the packed 64-bit voxel key
-//    (one IEEE double multiply by 1/s and a floor per axis) and seeds the
-//    index array; non-finite points get the all-ones sentinel key.
-// 2. stable LSD radix sort of (sort key, index), 8-bit digits, three kernels
-//    per pass (tile histograms, per-digit scan across tiles, ranked scatter).
-//    Ranks inside a tile come from 64-lane ballots, so equal digits keep
-//    their input order and the sort is stable. The sort key is a compacted
-//    form of the voxel key with the same order: each axis index minus the
-//    batch minimum, packed into just the bits the batch's ranges need, then
-//    an invalid-point bit, then the frame index (a batch is sorted by
-//    (frame, key)). A spinning scan needs ~24 key bits, so three or four
+// 1. key kernel: the packed 64-bit voxel key of every point (one IEEE double
+//    multiply by 1/s and a floor per axis), the batch's index ranges, and the
+//    call's counters cleared; non-finite points get the all-ones sentinel key.
+// 2. compose kernel: the sort key, and the digit histograms of every pass. The
+//    sort key is a compacted form of the voxel key with the same order: each
+//    axis index minus the batch minimum, packed into just the bits the batch's
+//    ranges need, then an invalid-point bit, then the frame index (a batch is
+//    sorted by (frame, key)). A spinning scan needs ~24 key bits, so four
 //    passes instead of eight. If the packed form does not fit 64 bits the
 //    frame index gets its own extra passes, read from the point's index.
-// 3. segmentation: voxel heads (key change or frame start), a scan over the
-//    heads, and scatter of keys / starts / counts; per-frame voxel ranges.
+// 3. stable LSD radix sort of (sort key, index), 8-bit digits, one kernel a
+//    pass: a tile's place among the tiles before it comes from their published
+//    digit counts (decoupled look-back). Ranks inside a tile come from 64-lane
+//    ballots, so equal digits keep their input order and the sort is stable.
+// 4. segment kernel: voxel heads (key change or frame start), numbered by a
+//    look-back of their counts; keys, starts, counts and frame ranges.
+//
+// The sort key's form stays on the device: four passes on 32-bit keys and the
+// segmentation are launched at once, a pass that the form does not have leaves
+// at once, and the host waits only for the results. For a form of more than 32
+// bits these leave at once, and passes on 64-bit keys and their segmentation
+// follow after that wait.
+//
+// Bound: up to ~300k points launches and waits, seven kernels' latencies of an uncached word
+// each; above that the four passes (28 us each for 3.7M points, of which 12.6 us are their
+// bytes, then tickets and the look-back). Whole calls, against a histogram, a scan and a
+// scatter kernel a pass on 64-bit keys, four segmentation kernels, two copies and a wait for
+// the key ranges: 16,384 points 104 -> 59 us, 131,072 117 -> 72, 524,288 134 -> 95, 64 frames
+// of 57,600 273 -> 204.
 #include <algorithm>
 #include <climits>
 
@@ -24,13 +38,27 @@
 namespace vgpr {
 namespace {
 
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 4;                       // per lane (4 x 256: several tiles per CU at 1M points)
-constexpr int kSortTile = kSortThreads * kSortItems;  // 1024 elements per block
-constexpr int kSortWaves = kSortThreads / 64;
+constexpr int kKeyThreads = 256;
+constexpr int kKeyItems = 4;
+constexpr int kKeyBlocks = 2048;                    // at most: every compose block reads all their partials
+constexpr int kComposeThreads = 1024;
+constexpr int kSmallCompose = 1, kLargeCompose = 2; // elements a thread reads together
+constexpr int kComposeBlocks = 256;
+constexpr int kSegItems = 8;
+constexpr int kSmallSeg = 256, kLargeSeg = 1024;    // threads
+constexpr int kMaxPasses = 12;                      // 8 of the packed key, 4 of the frame index
+constexpr int kNarrowPasses = 4;                    // sort keys of 32 bits
+// Tile of a sort pass: 1024 elements up to kSmallSort, where more tiles mean more CUs; 6144
+// above, where fewer tiles mean fewer tickets and a shorter look-back. All passes of a call,
+// 1024 against 6144: 131,072 points 29 / 38 us, 262,144 36 / 40, 524,288 55 / 43. At 3.7M
+// points: 4096 115 us, 6144 111, 8192 127.
+constexpr uint32_t kSmallSort = 1u << 18;
+constexpr int kSmallThreads = 512, kSmallItems = 2;
+constexpr int kLargeThreads = 1024, kLargeItems = 6;
+constexpr int kWideThreads = 512, kWideItems = 8;
 
-// Result words read back to the host after a voxelize call.
-enum { R_NVOX = 0, R_INVALID = 1, R_RANGE = 2, R_NVALID = 3, R_MIN = 4, R_MAX = 7, R_FRAMES = 10 };
+// Result words of a call, in pinned host memory: the kernels write them there.
+enum { R_NVOX = 0, R_INVALID = 1, R_RANGE = 2, R_PASSES = 3, R_FRAMES = 4 };
 
 // Compacted sort key: fields (k - kmin) in bx / by / bz bits (x highest), the
 // invalid flag at bit B = bx + by + bz, the frame index above it if embedded.
@@ -40,7 +68,9 @@ struct KeyForm {
   int bx, by, bz, B;
   int embed;           // frame index in bits [B + 1, ...)
   int key_passes;      // radix passes over the packed key
+  int passes;          // and with those over the frame index; 0 if the call is refused
   int morton;          // field bits interleaved (1) or concatenated (0)
+  int invalid, range;  // points that are not finite; whether one is out of the index range
   int64_t mn[3];       // per-axis minimum voxel index
 };
 
@@ -101,115 +131,230 @@ __device__ __forceinline__ int wave_max_i(int v) {
   return v;
 }
 
-// Voxel key of every point (packed, biased) and per-block min / max voxel index per axis.
-__global__ void __launch_bounds__(256) key_kernel(const float* __restrict__ xyz, int n, double inv_s,
-                                                  uint64_t* __restrict__ keys, int* __restrict__ part,
-                                                  unsigned long long* __restrict__ res) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool invalid = false;
-  bool range_err = false;
+// Per-block results of the key kernel.
+struct KeyPart {
+  int mn[3], mx[3];
+  int invalid, range;
+};
+
+// A grid-wide published word: tiles of one launch read each other's through these.
+template <typename T>
+__device__ __forceinline__ T peek(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void publish(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The next tile of a launch. Tiles are taken in the order in which their workgroups start, so
+// the tiles before a running one have all started, and a wait for what they publish ends.
+__device__ __forceinline__ uint32_t take_tile(uint32_t* ticket, uint32_t* smem) {
+  if (threadIdx.x == 0) *smem = atomicAdd(ticket, 1u);
+  __syncthreads();
+  const uint32_t t = __builtin_amdgcn_readfirstlane(*smem);
+  return t;
+}
+
+// Voxel key of every point (packed, biased), per-block index ranges and counts of unusable
+// points. Also clears the `zero_words` words of the sort's counters and brings the frame
+// offsets from pinned host memory: a memset and a copy would each be a launch of their own.
+__global__ void __launch_bounds__(kKeyThreads) key_kernel(const float* __restrict__ xyz, uint32_t n, double inv_s,
+                                                          uint64_t* __restrict__ keys, KeyPart* __restrict__ part,
+                                                          uint32_t* __restrict__ zero, size_t zero_words,
+                                                          const int64_t* __restrict__ h_fo, int64_t* __restrict__ fo,
+                                                          int nf) {
+  const size_t gid = (size_t)blockIdx.x * kKeyThreads + threadIdx.x;
+  const size_t gsz = (size_t)gridDim.x * kKeyThreads;
+  for (size_t j = gid; j < zero_words; j += gsz) zero[j] = 0u;
+  if (nf == 1) {  // no read across the bus
+    if (gid < 2) fo[gid] = gid ? (int64_t)n : 0;
+  } else {
+    for (size_t j = gid; j <= (size_t)nf; j += gsz) fo[j] = h_fo[j];
+  }
+  int invalid = 0, range = 0;
   int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN};
-  if (i < n) {
-    const float x = xyz[3 * (size_t)i + 0];
-    const float y = xyz[3 * (size_t)i + 1];
-    const float z = xyz[3 * (size_t)i + 2];
-    uint64_t key = kKeySentinel;
-    if (isfinite(x) && isfinite(y) && isfinite(z)) {
-      const double kx = floor(__dmul_rn((double)x, inv_s));
-      const double ky = floor(__dmul_rn((double)y, inv_s));
-      const double kz = floor(__dmul_rn((double)z, inv_s));
-      const double lim = (double)kKeyAxisLimit;
-      if (fabs(kx) > lim || fabs(ky) > lim || fabs(kz) > lim) {
-        range_err = true;
-      } else {
-        const int ix = (int)kx, iy = (int)ky, iz = (int)kz;
-        mn[0] = mx[0] = ix;
-        mn[1] = mx[1] = iy;
-        mn[2] = mx[2] = iz;
-        const uint64_t bx = (uint64_t)((int64_t)ix + kKeyBias);
-        const uint64_t by = (uint64_t)((int64_t)iy + kKeyBias);
-        const uint64_t bz = (uint64_t)((int64_t)iz + kKeyBias);
-        key = (bx << (2 * kKeyFieldBits)) | (by << kKeyFieldBits) | bz;
-      }
-    } else {
-      invalid = true;
-    }
-    keys[i] = key;
-  }
-  const unsigned long long inv_mask = __ballot(invalid);
-  const unsigned long long rng_mask = __ballot(range_err);
-  if (lane_id() == 0) {
-    if (inv_mask) atomicAdd(&res[R_INVALID], (unsigned long long)__popcll(inv_mask));
-    if (rng_mask) atomicOr(&res[R_RANGE], 1ull);
-  }
-  __shared__ int s[6][4];
-  const int w = threadIdx.x >> 6;
+  for (size_t base = (size_t)blockIdx.x * kKeyThreads * kKeyItems; base < n; base += gsz * kKeyItems) {
+    float c[kKeyItems][3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const int lo = wave_min_i(mn[a]), hi = wave_max_i(mx[a]);
-    if (lane_id() == 0) {
-      s[a][w] = lo;
-      s[3 + a][w] = hi;
+    for (int r = 0; r < kKeyItems; ++r) {
+      const size_t i = base + r * kKeyThreads + threadIdx.x;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) c[r][a] = i < n ? xyz[3 * i + a] : 0.0f;
     }
+#pragma unroll
+    for (int r = 0; r < kKeyItems; ++r) {
+      const size_t i = base + r * kKeyThreads + threadIdx.x;
+      if (i >= n) continue;
+      uint64_t key = kKeySentinel;
+      if (isfinite(c[r][0]) && isfinite(c[r][1]) && isfinite(c[r][2])) {
+        double k[3];
+        bool in = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          k[a] = floor(__dmul_rn((double)c[r][a], inv_s));
+          in = in && !(fabs(k[a]) > (double)kKeyAxisLimit);
+        }
+        if (in) {
+          key = 0;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            const int ia = (int)k[a];
+            mn[a] = min(mn[a], ia);
+            mx[a] = max(mx[a], ia);
+            key = (key << kKeyFieldBits) | (uint64_t)((int64_t)ia + kKeyBias);
+          }
+        } else {
+          range = 1;
+        }
+      } else {
+        ++invalid;
+      }
+      keys[i] = key;
+    }
+  }
+  __shared__ int s[8][kKeyThreads / 64];
+  const int w = threadIdx.x >> 6;
+  int red[8] = {wave_min_i(mn[0]), wave_min_i(mn[1]), wave_min_i(mn[2]), wave_max_i(mx[0]), wave_max_i(mx[1]),
+                wave_max_i(mx[2]), (int)wave_sum((uint32_t)invalid), wave_max_i(range)};
+  if (lane_id() == 0) {
+#pragma unroll
+    for (int a = 0; a < 8; ++a) s[a][w] = red[a];
   }
   __syncthreads();
-  if (threadIdx.x < 6) {
+  if (threadIdx.x < 8) {
     const int a = threadIdx.x;
     int r = s[a][0];
-    for (int k = 1; k < 4; ++k) r = a < 3 ? min(r, s[a][k]) : max(r, s[a][k]);
-    part[(size_t)blockIdx.x * 6 + a] = r;
+    for (int k = 1; k < kKeyThreads / 64; ++k) {
+      const int v = s[a][k];
+      r = a < 3 ? min(r, v) : a == 6 ? r + v : max(r, v);
+    }
+    reinterpret_cast<int*>(part + blockIdx.x)[a] = r;
   }
 }
 
-// Batch min / max per axis from the per-block partials.
-__global__ void __launch_bounds__(1024) minmax_kernel(const int* __restrict__ part, int nparts,
-                                                      unsigned long long* __restrict__ res) {
-  __shared__ int s[6][16];
-  int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN};
-  for (int b = threadIdx.x; b < nparts; b += 1024) {
+__device__ __forceinline__ int bits_of(int64_t r) { return r > 0 ? 64 - __clzll(r) : 0; }
+
+// The batch's sort key form, from the key kernel's partials; every thread of the block gets it.
+template <int NT>
+__device__ KeyForm key_form(const KeyPart* __restrict__ part, int nparts, uint32_t n, int nf, int morton) {
+  __shared__ int s[8][NT / 64];
+  int v[8] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN, 0, 0};
+  for (int b = threadIdx.x; b < nparts; b += NT) {
+    const KeyPart p = part[b];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      mn[a] = min(mn[a], part[(size_t)b * 6 + a]);
-      mx[a] = max(mx[a], part[(size_t)b * 6 + 3 + a]);
+      v[a] = min(v[a], p.mn[a]);
+      v[3 + a] = max(v[3 + a], p.mx[a]);
     }
+    v[6] += p.invalid;
+    v[7] |= p.range;
   }
-  const int w = threadIdx.x >> 6;
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    const int r = a < 3 ? wave_min_i(v[a]) : a == 6 ? (int)wave_sum((uint32_t)v[a]) : wave_max_i(v[a]);
+    if (lane_id() == 0) s[a][threadIdx.x >> 6] = r;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    int r = s[a][0];
+#pragma unroll
+    for (int k = 1; k < NT / 64; ++k) r = a < 3 ? min(r, s[a][k]) : a == 6 ? r + s[a][k] : max(r, s[a][k]);
+    v[a] = __builtin_amdgcn_readfirstlane(r);
+  }
+  KeyForm kf{};
+  kf.invalid = v[6];
+  kf.range = v[7];
+  const bool any_valid = (uint32_t)v[6] < n;
+  int b3[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const int lo = wave_min_i(mn[a]), hi = wave_max_i(mx[a]);
-    if (lane_id() == 0) {
-      s[a][w] = lo;
-      s[3 + a][w] = hi;
+    kf.mn[a] = any_valid ? v[a] : 0;
+    b3[a] = any_valid ? bits_of((int64_t)v[3 + a] - v[a]) : 0;
+  }
+  kf.bx = b3[0];
+  kf.by = b3[1];
+  kf.bz = b3[2];
+  kf.B = b3[0] + b3[1] + b3[2];
+  const int bf = nf > 1 ? bits_of(nf - 1) : 0;
+  kf.embed = kf.B + 1 + bf <= 64 ? 1 : 0;
+  kf.key_passes = (kf.B + 1 + (kf.embed ? bf : 0) + 7) / 8;
+  kf.passes = v[7] ? 0 : kf.key_passes + (kf.embed ? 0 : (bf + 7) / 8);
+  kf.morton = morton;
+  return kf;
+}
+
+__device__ __forceinline__ uint64_t pack_sort_key(uint64_t key, const KeyForm& kf) {
+  if (key == kKeySentinel) return 1ull << kf.B;
+  const int64_t mask = (int64_t(1) << kKeyFieldBits) - 1;
+  const uint64_t ux = (uint64_t)((int64_t)((key >> (2 * kKeyFieldBits)) & mask) - kKeyBias - kf.mn[0]);
+  const uint64_t uy = (uint64_t)((int64_t)((key >> kKeyFieldBits) & mask) - kKeyBias - kf.mn[1]);
+  const uint64_t uz = (uint64_t)((int64_t)(key & mask) - kKeyBias - kf.mn[2]);
+  return kf.morton ? interleave3(ux, uy, uz, kf) : (ux << (kf.by + kf.bz)) | (uy << kf.bz) | uz;
+}
+
+// Packed key -> compacted sort key, and every pass's digit histogram. Keys of up to 32 bits go
+// to `narrow`, wider ones stay in place. A scan's neighbours often share their digits, and
+// LDS adds to one word go one by one: only the first lane of a run adds, with its length.
+template <int ITEMS>
+__global__ void __launch_bounds__(kComposeThreads) compose_kernel(
+    uint64_t* __restrict__ keys, uint32_t* __restrict__ narrow, uint32_t n, const KeyPart* __restrict__ part, int nparts,
+    int morton, const int64_t* __restrict__ fo, int nf, KeyForm* __restrict__ form, uint32_t* __restrict__ hist) {
+  constexpr int kTile = kComposeThreads * ITEMS;
+  __shared__ uint32_t h[kMaxPasses * 256];
+  const KeyForm kf = key_form<kComposeThreads>(part, nparts, n, nf, morton);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *form = kf;
+  if (kf.range) return;
+  for (int j = threadIdx.x; j < kf.passes * 256; j += kComposeThreads) h[j] = 0;
+  __syncthreads();
+  // a block's elements are consecutive, so its frames are too
+  const size_t tiles = ((size_t)n + kTile - 1) / kTile;
+  const size_t b0 = tiles * blockIdx.x / gridDim.x * kTile;
+  const size_t b1 = tiles * (blockIdx.x + 1) / gridDim.x * kTile;
+  const bool frames = kf.embed && nf > 1;
+  int f = frames ? frame_of((uint32_t)(b0 < n ? b0 : n - 1), fo, nf) : 0;
+  const unsigned long long upto = ~0ull >> (63 - lane_id());
+  for (size_t base = b0; base < b1; base += kTile) {
+    uint64_t k[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const size_t i = base + r * kComposeThreads + threadIdx.x;
+      k[r] = i < n ? keys[i] : kKeySentinel;
+    }
+    if (frames)
+      while (f < nf - 1 && fo[f + 1] <= (int64_t)base) ++f;
+    const int64_t frame_end = frames ? fo[f + 1] : 0;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const size_t i = base + r * kComposeThreads + threadIdx.x;
+      const bool in = i < n;
+      uint64_t tk = pack_sort_key(k[r], kf);
+      if (frames && in)
+        tk |= (uint64_t)((int64_t)i < frame_end ? f : frame_of((uint32_t)i, fo, nf)) << (kf.B + 1);
+      if (in) {
+        if (kf.passes <= kNarrowPasses) narrow[i] = (uint32_t)tk;
+        else keys[i] = tk;
+      }
+      const unsigned long long act = __ballot(in);
+      for (int p = 0; p < kf.passes; ++p) {
+        const uint32_t d = in ? digit_of(tk, (uint32_t)i, p, kf.key_passes, fo, nf) : 256u;
+        const uint32_t prev = __shfl_up(d, 1, 64);
+        const bool first = lane_id() == 0 || prev != d;
+        const unsigned long long heads = __ballot(first);
+        if (first && in) {
+          const unsigned long long after = heads & ~upto;
+          const int end = after ? __ffsll(after) - 1 : __popcll(act);
+          atomicAdd(&h[p * 256 + d], (uint32_t)(end - lane_id()));
+        }
+      }
     }
   }
   __syncthreads();
-  if (threadIdx.x < 6) {
-    const int a = threadIdx.x;
-    int r = s[a][0];
-    for (int k = 1; k < 16; ++k) r = a < 3 ? min(r, s[a][k]) : max(r, s[a][k]);
-    res[(a < 3 ? R_MIN : R_MAX - 3) + a] = (unsigned long long)(long long)r;
+  for (int j = threadIdx.x; j < kf.passes * 256; j += kComposeThreads) {
+    const uint32_t c = h[j];
+    if (c) atomicAdd(&hist[j], c);
   }
-}
-
-// Packed key -> compacted sort key (in place); seeds the index array the first pass reads.
-__global__ void __launch_bounds__(256) compose_kernel(uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, int n,
-                                                      KeyForm kf, const int64_t* __restrict__ fo, int nf) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  vals[i] = (uint32_t)i;
-  const uint64_t key = keys[i];
-  uint64_t tk;
-  if (key == kKeySentinel) {
-    tk = 1ull << kf.B;
-  } else {
-    const int64_t mask = (int64_t(1) << kKeyFieldBits) - 1;
-    const uint64_t ux = (uint64_t)((int64_t)((key >> (2 * kKeyFieldBits)) & mask) - kKeyBias - kf.mn[0]);
-    const uint64_t uy = (uint64_t)((int64_t)((key >> kKeyFieldBits) & mask) - kKeyBias - kf.mn[1]);
-    const uint64_t uz = (uint64_t)((int64_t)(key & mask) - kKeyBias - kf.mn[2]);
-    tk = kf.morton ? interleave3(ux, uy, uz, kf) : (ux << (kf.by + kf.bz)) | (uy << kf.bz) | uz;
-  }
-  if (kf.embed && nf > 1) tk |= (uint64_t)frame_of((uint32_t)i, fo, nf) << (kf.B + 1);
-  keys[i] = tk;
 }
 
 // Compacted sort key -> packed voxel key.
@@ -229,213 +374,332 @@ __device__ __forceinline__ uint64_t unpack_sort_key(uint64_t tk, const KeyForm& 
          (uint64_t)(kz + kKeyBias);
 }
 
-// Per-tile digit histogram, stored digit-major: hist[d * nblocks + b].
-__global__ void __launch_bounds__(kSortThreads) radix_upsweep(const uint64_t* __restrict__ keys,
-                                                              const uint32_t* __restrict__ vals, int n, int pass,
-                                                              int key_passes, const int64_t* __restrict__ fo, int nf,
-                                                              uint32_t* __restrict__ hist, int nblocks) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int base = blockIdx.x * kSortTile;
-#pragma unroll 4
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = base + r * kSortThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[digit_of(keys[i], vals[i], pass, key_passes, fo, nf)], 1u);
-  }
-  __syncthreads();
-  hist[(size_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+// What tiles publish for one digit. A tile: 0 until known, then its count + 1. A group of 16
+// tiles: the sum of their counts, with the number of tiles in it from bit 24. A group with all
+// before it: 0 until known, then the count with the top bit. A tile adds up the tiles before
+// it in its group and the groups before that, 16 words of a digit at a time: with single tiles
+// alone the last of 450 tiles walks 28 steps of an uncached read (~0.5 us), with groups three.
+constexpr uint32_t kInclusive = 0x80000000u;
+constexpr int kGroup = 16;
+
+struct Published {
+  uint32_t *tiles, *groups, *upto;  // rows of 256 digits
+};
+
+__host__ __device__ __forceinline__ size_t published_rows(uint32_t max_tiles) {
+  return (size_t)max_tiles + 2 * ((size_t)(max_tiles + kGroup - 1) / kGroup);
 }
 
-// Block d: exclusive scan of digit d's row across tiles, in place; row total out.
-__global__ void __launch_bounds__(1024) radix_rowscan(uint32_t* __restrict__ hist, int nblocks,
-                                                      uint32_t* __restrict__ row_total) {
-  __shared__ uint32_t smem[17];
-  uint32_t* row = hist + (size_t)blockIdx.x * nblocks;
-  uint32_t carry = 0;
-  for (int s = 0; s < nblocks; s += 1024) {
-    const int i = s + threadIdx.x;
-    const uint32_t v = i < nblocks ? row[i] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_sum<1024>(v, smem, &tot);
-    if (i < nblocks) row[i] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) row_total[blockIdx.x] = carry;
+__device__ __forceinline__ Published published(uint32_t* status, int half, uint32_t max_tiles) {
+  uint32_t* t = status + half * published_rows(max_tiles) * 256;
+  uint32_t* g = t + (size_t)max_tiles * 256;
+  return {t, g, g + (size_t)((max_tiles + kGroup - 1) / kGroup) * 256};
 }
 
-// Ranked scatter. Element order inside a tile is (wave, round, lane), which is
-// the input order, so ranks from ballots preserve stability.
-__global__ void __launch_bounds__(kSortThreads) radix_downsweep(
-    const uint64_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint64_t* __restrict__ keys_out,
-    uint32_t* __restrict__ vals_out, int n, int pass, int key_passes, const int64_t* __restrict__ fo, int nf,
-    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ row_total, int nblocks) {
-  __shared__ uint32_t cnt[kSortWaves][256];
-  __shared__ uint32_t scan_smem[kSortWaves + 1];
-  const int lane = lane_id();
-  const int wave = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < kSortWaves * 256; i += kSortThreads) (&cnt[0][0])[i] = 0;
-  // global start of each digit: exclusive scan of the row totals
-  uint32_t dtot;
-  const uint32_t digit_start = block_exclusive_sum<kSortThreads>(row_total[threadIdx.x], scan_smem, &dtot);
-  const uint32_t tile_base_for_digit = digit_start + hist[(size_t)threadIdx.x * nblocks + blockIdx.x];
-  __syncthreads();
-
-  const int base = blockIdx.x * kSortTile + wave * 64 * kSortItems;
-  uint64_t k[kSortItems];
-  uint32_t v[kSortItems];
-  uint32_t d[kSortItems];
-  uint32_t rank[kSortItems];
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
+// Digit `d`'s elements in the tiles before `tile`.
+__device__ __forceinline__ uint32_t before_tile(const Published& pub, uint32_t tile, int d) {
+  const uint32_t group = tile / kGroup, in_group = tile % kGroup;
+  uint32_t excl = 0;
+  {
+    const uint32_t* rows = pub.tiles + (size_t)group * kGroup * 256 + d;
+    uint32_t w[kGroup - 1];
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = base + r * 64 + lane;
-    const bool valid = i < n;
-    k[r] = valid ? keys_in[i] : 0ull;
-    v[r] = valid ? vals_in[i] : 0u;
-    d[r] = valid ? digit_of(k[r], v[r], pass, key_passes, fo, nf) : 0u;
+    for (int j = 0; j < kGroup - 1; ++j) w[j] = j < (int)in_group ? peek(rows + 256 * j) : 1u;
+#pragma unroll
+    for (int j = 0; j < kGroup - 1; ++j) {
+      while (w[j] == 0u) {
+        __builtin_amdgcn_s_sleep(1);
+        w[j] = peek(rows + 256 * j);
+      }
+      excl += w[j] - 1u;
+    }
+  }
+  for (int64_t g = (int64_t)group - 1; g >= 0; g -= kGroup) {
+    // groups g, g - 1, .. ; the farthest is asked for the prefix it closes
+    const int64_t far = g - (kGroup - 1) > 0 ? g - (kGroup - 1) : 0;
+    uint32_t w[kGroup];
+    const uint32_t up = peek(pub.upto + (size_t)far * 256 + d);
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) w[j] = g - j >= 0 ? peek(pub.groups + (size_t)(g - j) * 256 + d) : 0u;
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) {
+      if (g - j < 0 || (g - j == far && up)) continue;
+      while ((w[j] >> 24) != kGroup) {
+        __builtin_amdgcn_s_sleep(1);
+        w[j] = peek(pub.groups + (size_t)(g - j) * 256 + d);
+      }
+      excl += w[j] & 0xFFFFFFu;
+    }
+    if (up) {
+      excl += up & ~kInclusive;
+      break;
+    }
+  }
+  return excl;
+}
+
+// One radix pass. Element order inside a tile is (wave, round, lane), which is the input
+// order, so ranks from ballots preserve stability. The tile is put in order in LDS first, so
+// the stores of a digit's run are consecutive. Pass p's words are in half p & 1; it clears
+// the other half, which pass p - 1 is done with, for pass p + 1.
+template <typename K, int NT, int ITEMS>
+__global__ void __launch_bounds__(NT) radix_pass(K* __restrict__ keys_a, K* __restrict__ keys_b,
+                                                 uint32_t* __restrict__ perm, uint32_t* __restrict__ vals_tmp,
+                                                 uint32_t n, int pass, const KeyForm* __restrict__ form,
+                                                 const int64_t* __restrict__ fo, int nf,
+                                                 const uint32_t* __restrict__ hist, uint32_t* __restrict__ status,
+                                                 uint32_t max_tiles, uint32_t* __restrict__ tickets) {
+  constexpr bool kNarrow = sizeof(K) == 4;
+  constexpr int kWaves = NT / 64;
+  constexpr uint32_t kTile = NT * ITEMS;
+  __shared__ uint32_t cnt[kWaves][256];
+  __shared__ uint32_t scan_smem[kWaves + 1];
+  __shared__ uint32_t gbase[256];
+  __shared__ K skey[kTile];
+  __shared__ uint32_t sval[kTile];
+  __shared__ uint32_t s_tile;
+  const int passes = form->passes, key_passes = form->key_passes;
+  if (pass >= passes || (passes <= kNarrowPasses) != kNarrow) return;
+  const K* __restrict__ keys_in = (pass & 1) ? keys_b : keys_a;
+  K* __restrict__ keys_out = (pass & 1) ? keys_a : keys_b;
+  // the last pass writes the indices into perm; pass 0 reads none (element i is point i)
+  const bool to_perm = ((passes - 1 - pass) & 1) == 0;
+  const uint32_t* vals_in = to_perm ? vals_tmp : perm;
+  uint32_t* vals_out = to_perm ? perm : vals_tmp;
+  auto digit = [&](K key, uint32_t val) -> uint32_t {
+    if (kNarrow) return (uint32_t)(key >> (8 * pass)) & 0xFFu;
+    return digit_of(key, val, pass, key_passes, fo, nf);
+  };
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+
+  for (int i = tid; i < kWaves * 256; i += NT) (&cnt[0][0])[i] = 0;
+  const uint32_t tile = take_tile(&tickets[pass], &s_tile);
+  const Published pub = published(status, pass & 1, max_tiles);
+  const uint32_t group = tile / kGroup;
+  if (tid < 256) {
+    const Published next = published(status, (pass + 1) & 1, max_tiles);
+    next.tiles[(size_t)tile * 256 + tid] = 0;
+    if (tile % kGroup == 0) next.groups[(size_t)group * 256 + tid] = next.upto[(size_t)group * 256 + tid] = 0;
+  }
+
+  const uint32_t base = tile * kTile + wave * 64 * ITEMS;
+  K k[ITEMS];
+  uint32_t v[ITEMS], old[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t i = base + r * 64 + lane;
+    k[r] = i < n ? keys_in[i] : K(0);
+    v[r] = i < n ? (pass ? vals_in[i] : i) : 0u;
+  }
+  // global start of each digit
+  uint32_t dtot;
+  const uint32_t digit_start = block_exclusive_sum<NT>(tid < 256 ? hist[pass * 256 + tid] : 0u, scan_smem,
+                                                                 &dtot);
+  // A wave's rounds one after another: the first lane of each digit adds the round's count to
+  // the wave's counter. The adds need no answer until all are issued.
+  const unsigned long long lt_mask = (1ull << lane) - 1ull;
+  uint32_t from[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const bool valid = base + r * 64 + lane < n;
+    const uint32_t d = valid ? digit(k[r], v[r]) : 0u;
     unsigned long long peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const bool bit = (d[r] >> b) & 1u;
+      const bool bit = (d >> b) & 1u;
       const unsigned long long bal = __ballot(valid && bit);
       peers &= bit ? bal : ~bal;
     }
-    const uint32_t before = (uint32_t)__popcll(peers & lt_mask);
-    const uint32_t total = (uint32_t)__popcll(peers);
-    const bool leader = valid && before == 0;
-    uint32_t old = 0;
-    if (valid) old = cnt[wave][d[r]];
-    rank[r] = old + before;
-    __builtin_amdgcn_wave_barrier();
-    if (leader) cnt[wave][d[r]] = old + total;
-    __builtin_amdgcn_wave_barrier();
+    rank[r] = (uint32_t)__popcll(peers & lt_mask);
+    from[r] = valid ? (uint32_t)__ffsll(peers) - 1u : 0u;
+    old[r] = 0;
+    if (valid && rank[r] == 0) old[r] = atomicAdd(&cnt[wave][d], (uint32_t)__popcll(peers));
+  }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) rank[r] += __shfl(old[r], from[r], 64);
+  __syncthreads();
+  uint32_t sum = 0;
+  if (tid < 256) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t c = cnt[w][tid];
+      cnt[w][tid] = sum;
+      sum += c;
+    }
+    publish(&pub.tiles[(size_t)tile * 256 + tid], sum + 1u);
+    atomicAdd(&pub.groups[(size_t)group * 256 + tid], sum + (1u << 24));
+  }
+  const uint32_t local = block_exclusive_sum<NT>(sum, scan_smem, &dtot);
+  if (tid < 256) {
+    const uint32_t excl = before_tile(pub, tile, tid);
+    if (tile % kGroup == kGroup - 1) publish(&pub.upto[(size_t)group * 256 + tid], kInclusive | (excl + sum));
+    gbase[tid] = digit_start + excl - local;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) cnt[w][tid] += local;
   }
   __syncthreads();
-  // per digit: offset of each wave inside the tile, then the tile's global base
-  {
-    const int t = threadIdx.x;  // digit
-    uint32_t run = tile_base_for_digit;
 #pragma unroll
-    for (int w = 0; w < kSortWaves; ++w) {
-      const uint32_t c = cnt[w][t];
-      cnt[w][t] = run;
-      run += c;
+  for (int r = 0; r < ITEMS; ++r) {
+    if (base + r * 64 + lane < n) {
+      const uint32_t p = cnt[wave][digit(k[r], v[r])] + rank[r];
+      skey[p] = k[r];
+      sval[p] = v[r];
     }
   }
   __syncthreads();
+  const uint32_t have = min(kTile, n - tile * kTile);
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = base + r * 64 + lane;
-    const uint32_t dst = cnt[wave][d[r]] + rank[r];
-    if (i < n && dst < (uint32_t)n) {
-      keys_out[dst] = k[r];
-      vals_out[dst] = v[r];
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t p = r * NT + tid;
+    if (p < have) {
+      const K kk = skey[p];
+      const uint32_t vv = sval[p];
+      const uint32_t dst = gbase[digit(kk, vv)] + p;
+      if (dst < n) {
+        keys_out[dst] = kk;
+        vals_out[dst] = vv;
+      }
     }
   }
 }
 
 __device__ __forceinline__ bool sort_key_valid(uint64_t k, const KeyForm& kf) { return ((k >> kf.B) & 1ull) == 0; }
 
-__device__ __forceinline__ bool is_head(const uint64_t* keys, int i, const KeyForm& kf, const int64_t* fo, int nf) {
-  const uint64_t k = keys[i];
-  if (!sort_key_valid(k, kf)) return false;
-  if (i == 0) return true;
-  if (keys[i - 1] != k) return true;
-  return !kf.embed && nf > 1 && frame_of((uint32_t)i, fo, nf) != frame_of((uint32_t)(i - 1), fo, nf);
+// Whether sorted elements i - 1 and i, with keys a and b, are of one voxel (b is a valid one).
+__device__ __forceinline__ bool same_voxel(uint64_t a, uint64_t b, uint32_t i, const KeyForm& kf, const int64_t* fo,
+                                           int nf) {
+  if (a != b) return false;
+  return kf.embed || nf == 1 || frame_of(i, fo, nf) == frame_of(i - 1, fo, nf);
 }
 
-__device__ __forceinline__ bool is_tail(const uint64_t* keys, int i, int n, const KeyForm& kf, const int64_t* fo,
-                                        int nf) {
-  const uint64_t k = keys[i];
-  if (!sort_key_valid(k, kf)) return false;
-  if (i == n - 1) return true;
-  if (keys[i + 1] != k) return true;
-  return !kf.embed && nf > 1 && frame_of((uint32_t)(i + 1), fo, nf) != frame_of((uint32_t)i, fo, nf);
-}
+// A tile's published word of the segmentation: 0 until known, then bit 62 (the tile alone) or
+// bit 63 (with all before it), the voxel heads in bits 31..61 and the last head's position + 1
+// in bits 0..30 (0: no head).
+constexpr unsigned long long kSegAlone = 1ull << 62, kSegUpTo = 1ull << 63, kSegPos = (1ull << 31) - 1;
 
-__global__ void __launch_bounds__(kSortThreads) seg_reduce(const uint64_t* __restrict__ keys, int n, KeyForm kf,
-                                                           const int64_t* __restrict__ fo, int nf,
-                                                           uint32_t* __restrict__ block_sums) {
-  uint32_t c = 0;
-  const int base = blockIdx.x * kSortTile;
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = base + r * kSortThreads + threadIdx.x;
-    if (i < n && is_head(keys, i, kf, fo, nf)) ++c;
+// Voxel heads are numbered in order; the voxel's last element writes its count, with the
+// head's position from the tile's own list or from the look-back. Frame f's first voxel is
+// the number of heads before element fo[f].
+template <typename K, int NT>
+__global__ void __launch_bounds__(NT) segment_kernel(
+    const K* __restrict__ keys_a, const K* __restrict__ keys_b, uint32_t n, const KeyForm* __restrict__ form, const int64_t* __restrict__ fo, int nf, unsigned long long* __restrict__ status,
+    uint32_t ntiles, uint32_t* __restrict__ ticket, int64_t cap, uint64_t* __restrict__ out_keys,
+    int32_t* __restrict__ out_off, int32_t* __restrict__ out_cnt, unsigned long long* __restrict__ h_res) {
+  constexpr int kTile = NT * kSegItems;
+  __shared__ uint32_t scan_smem[NT / 64 + 1];
+  __shared__ uint32_t pos[kTile];
+  __shared__ uint32_t s_tile;
+  __shared__ unsigned long long s_before;
+  const KeyForm kf = *form;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    h_res[R_INVALID] = (unsigned long long)kf.invalid;
+    h_res[R_RANGE] = (unsigned long long)kf.range;
+    h_res[R_PASSES] = (unsigned long long)kf.passes;
   }
-  c = wave_sum(c);
-  __shared__ uint32_t s[kSortWaves];
-  if (lane_id() == 0) s[threadIdx.x >> 6] = c;
+  if (kf.passes == 0 || (kf.passes <= kNarrowPasses) != (sizeof(K) == 4)) return;
+  const K* __restrict__ keys = (kf.passes & 1) ? keys_b : keys_a;
+  const int tid = threadIdx.x;
+  const uint32_t tile = take_tile(ticket, &s_tile);
+  const uint32_t t0 = tile * kTile;
+  const uint32_t first = t0 + tid * kSegItems;
+  // a thread's elements are consecutive, with one on either side
+  uint64_t k[kSegItems + 2];
+#pragma unroll
+  for (int r = 0; r < kSegItems + 2; ++r) {
+    const uint32_t i = first + r - 1;  // wraps below element 0
+    k[r] = i < n ? keys[i] : 0ull;
+  }
+  uint32_t head = 0, tail = 0;  // bit r: element first + r
+#pragma unroll
+  for (int r = 0; r < kSegItems; ++r) {
+    const uint32_t i = first + r;
+    if (i < n && sort_key_valid(k[r + 1], kf)) {
+      if (i == 0 || !same_voxel(k[r], k[r + 1], i, kf, fo, nf)) head |= 1u << r;
+      if (i == n - 1 || !same_voxel(k[r + 1], k[r + 2], i + 1, kf, fo, nf)) tail |= 1u << r;
+    }
+  }
+  uint32_t heads;
+  const uint32_t ex = block_exclusive_sum<NT>((uint32_t)__popc(head), scan_smem, &heads);
+  {
+    uint32_t o = ex;
+#pragma unroll
+    for (int r = 0; r < kSegItems; ++r)
+      if (head >> r & 1u) pos[o++] = first + r;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < kSortWaves; ++w) t += s[w];
-    block_sums[blockIdx.x] = t;
-  }
-}
-
-__global__ void __launch_bounds__(1024) seg_scan_blocks(uint32_t* __restrict__ block_sums, int nblocks,
-                                                        unsigned long long* __restrict__ res) {
-  __shared__ uint32_t smem[17];
-  uint32_t carry = 0;
-  for (int s = 0; s < nblocks; s += 1024) {
-    const int i = s + threadIdx.x;
-    const uint32_t v = i < nblocks ? block_sums[i] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_sum<1024>(v, smem, &tot);
-    if (i < nblocks) block_sums[i] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) res[R_NVOX] = carry;
-}
-
-// Heads write key and start; tails write end (turned into a count later).
-__global__ void __launch_bounds__(kSortThreads) seg_scatter(const uint64_t* __restrict__ keys, int n, KeyForm kf,
-                                                            const int64_t* __restrict__ fo, int nf,
-                                                            const uint32_t* __restrict__ block_base,
-                                                            int64_t cap, uint64_t* __restrict__ out_keys,
-                                                            int32_t* __restrict__ out_off,
-                                                            int32_t* __restrict__ out_cnt) {
-  __shared__ uint32_t smem[kSortWaves + 1];
-  const int base = blockIdx.x * kSortTile;
-  uint32_t carry = block_base[blockIdx.x];
-  for (int r = 0; r < kSortItems; ++r) {
-    const int i = base + r * kSortThreads + threadIdx.x;
-    const bool h = i < n && is_head(keys, i, kf, fo, nf);
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_sum<kSortThreads>(h ? 1u : 0u, smem, &tot);
-    const uint32_t vid_incl = carry + ex + (h ? 1u : 0u);  // heads up to and including i
-    if (h && (int64_t)(vid_incl - 1) < cap) {
-      out_keys[vid_incl - 1] = unpack_sort_key(keys[i], kf);
-      out_off[vid_incl - 1] = i;
-    }
-    if (i < n && is_tail(keys, i, n, kf, fo, nf) && (int64_t)(vid_incl - 1) < cap) out_cnt[vid_incl - 1] = i + 1;
-    carry += tot;
-  }
-}
-
-__global__ void __launch_bounds__(256) seg_finish(const int32_t* __restrict__ out_off, int32_t* __restrict__ out_cnt,
-                                                  int64_t cap, const int64_t* __restrict__ fo, int nf,
-                                                  unsigned long long* __restrict__ res) {
-  const int64_t nvox = (int64_t)res[R_NVOX];
-  const int64_t lim = nvox < cap ? nvox : cap;
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < lim) out_cnt[v] -= out_off[v];
-  // frame f's first voxel = number of voxels starting before fo[f]
-  if (v <= nf) {
-    int64_t r;
-    if (v == 0) r = 0;
-    else if (v == nf || nvox > cap) r = (v == nf) ? nvox : 0;
-    else {
-      int64_t lo = 0, hi = lim;  // first voxel with start >= fo[v]
-      const int64_t target = fo[v];
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)out_off[mid] < target) lo = mid + 1; else hi = mid;
+  if (tid < 64) {
+    const unsigned long long own = ((unsigned long long)heads << 31) | (heads ? pos[heads - 1] + 1ull : 0ull);
+    if (tid == 0) publish(&status[tile], (tile == 0 ? kSegUpTo : kSegAlone) | own);
+    // the 64 tiles before, then the 64 before those, until one that holds its own prefix
+    unsigned long long count = 0, last = 0;
+    int64_t back = (int64_t)tile - 1;
+    while (back >= 0) {
+      const int64_t t = back - tid;
+      unsigned long long w;
+      unsigned long long up;
+      do {
+        w = t >= 0 ? peek(&status[t]) : kSegUpTo;
+        up = __ballot((w & kSegUpTo) != 0);
+        // lanes past the first prefix are not needed
+        const unsigned long long need = up ? ((up & -up) << 1) - 1ull : ~0ull;
+        if ((__ballot(w != 0) & need) == need) break;
+        __builtin_amdgcn_s_sleep(1);
+      } while (true);
+      const int stop = up ? __ffsll(up) - 1 : 63;
+      unsigned long long c = tid <= stop ? (w >> 31) & kSegPos : 0ull;
+      unsigned long long p = tid <= stop ? w & kSegPos : 0ull;  // positions grow with the tile: the maximum is the last
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        c += __shfl_xor(c, d, 64);
+        const unsigned long long q = __shfl_xor(p, d, 64);
+        p = q > p ? q : p;
       }
-      r = lo;
+      count += c;
+      last = p > last ? p : last;
+      if (up) break;
+      back -= 64;
     }
-    res[R_FRAMES + v] = (unsigned long long)r;
+    if (tid == 0) {
+      const unsigned long long all = ((count + heads) << 31) | (heads ? own & kSegPos : last);
+      if (tile) publish(&status[tile], kSegUpTo | all);
+      s_before = (count << 31) | last;
+      if (tile == ntiles - 1) h_res[R_NVOX] = count + heads;
+    }
+  }
+  __syncthreads();
+  const uint32_t vbase = (uint32_t)(s_before >> 31);
+  uint32_t o = ex;  // heads of the tile before element first + r
+#pragma unroll
+  for (int r = 0; r < kSegItems; ++r) {
+    const uint32_t i = first + r;
+    if (head >> r & 1u) {
+      const uint32_t vid = vbase + o++;
+      if ((int64_t)vid < cap) {
+        out_keys[vid] = unpack_sort_key(k[r + 1], kf);
+        out_off[vid] = (int32_t)i;
+      }
+    }
+    if (tail >> r & 1u) {
+      const uint32_t vid = vbase + o - 1;
+      const uint32_t start = o ? pos[o - 1] : (uint32_t)(s_before & kSegPos) - 1u;
+      if ((int64_t)vid < cap) out_cnt[vid] = (int32_t)(i + 1 - start);
+    }
+  }
+  // frames that start in this tile; the last tile also has those that start at n
+  const int64_t end = tile == ntiles - 1 ? (int64_t)n + 1 : (int64_t)t0 + kTile;
+  int lo = 0, hi = nf + 1;  // first f with fo[f] >= t0
+  while (lo < hi) {
+    const int m = (lo + hi) >> 1;
+    if (fo[m] < (int64_t)t0) lo = m + 1; else hi = m;
+  }
+  for (int64_t f = (int64_t)lo + tid; f <= nf && fo[f] < end; f += NT) {
+    const int64_t target = fo[f];
+    uint32_t a = 0, b = heads;  // heads of the tile before the target
+    while (a < b) {
+      const uint32_t m = (a + b) >> 1;
+      if ((int64_t)pos[m] < target) a = m + 1; else b = m;
+    }
+    h_res[R_FRAMES + f] = (unsigned long long)vbase + a;
   }
 }
 
@@ -462,123 +726,102 @@ vgpr_status voxelize_impl(vgpr_ctx* ctx, const float* d_xyz, int64_t n_pts, cons
     if (n_frames > 1) return fail(ctx, VGPR_E_INVALID, "h_frame_offsets is NULL with n_frames > 1");
     fo[1] = n_pts;
   }
-  const int n = (int)n_pts;
-  const int nblocks = n ? (n + kSortTile - 1) / kSortTile : 1;
-  const size_t res_words = R_FRAMES + nf + 1;
+  const uint32_t n = (uint32_t)n_pts;
+  const size_t res_words = R_FRAMES + (size_t)nf + 1;
+  const bool small = n <= kSmallSort;
+  const uint32_t min_tile =
+      small ? kSmallThreads * kSmallItems : std::min(kLargeThreads * kLargeItems, kWideThreads * kWideItems);
+  const uint32_t max_tiles = (uint32_t)((n_pts + min_tile - 1) / min_tile);
+  const uint32_t nseg = (uint32_t)((n_pts + kSegItems * (small ? kSmallSeg : kLargeSeg) - 1) / (kSegItems * (small ? kSmallSeg : kLargeSeg)));
+  const uint32_t kblocks = (uint32_t)std::min<int64_t>((n_pts + kKeyThreads * kKeyItems - 1) / (kKeyThreads * kKeyItems),
+                                                       kKeyBlocks);
+  // words cleared by the key kernel: segmentation look-back, histograms, tickets, the first pass's look-back
+  const size_t o_hist = 2 * (size_t)nseg, o_ticket = o_hist + 256 * kMaxPasses, o_status = o_ticket + kMaxPasses + 2;
+  const size_t zero_words = o_status + 256 * published_rows(max_tiles);
+  const size_t words = zero_words + 256 * published_rows(max_tiles);
 
-  const int kblocks = n ? (n + 255) / 256 : 1;
-  size_t need = work_offset + Carver::round(sizeof(uint64_t) * (size_t)n) * 2 +
-                Carver::round(sizeof(uint32_t) * (size_t)n) + Carver::round(sizeof(uint32_t) * 256 * nblocks) +
-                Carver::round(sizeof(uint32_t) * 256) + Carver::round(sizeof(uint32_t) * nblocks) +
-                Carver::round(sizeof(int) * 6 * (size_t)kblocks) + Carver::round(sizeof(int64_t) * (nf + 1)) +
-                Carver::round(sizeof(unsigned long long) * res_words) + 4096;
+  const size_t need = work_offset + Carver::round(sizeof(uint64_t) * (size_t)n) * 2 +
+                      Carver::round(sizeof(uint32_t) * (size_t)n) + Carver::round(sizeof(uint32_t) * words) +
+                      Carver::round(sizeof(KeyPart) * (size_t)kblocks) + Carver::round(sizeof(int64_t) * ((size_t)nf + 1)) +
+                      Carver::round(sizeof(KeyForm)) + 4096;
   vgpr_status st = reserve_work(ctx, need);
   if (st != VGPR_OK) return st;
-  st = reserve_pinned(ctx, sizeof(int64_t) * (nf + 1) + sizeof(unsigned long long) * res_words + 64);
+  st = reserve_pinned(ctx, sizeof(int64_t) * ((size_t)nf + 1) + sizeof(unsigned long long) * res_words + 64);
   if (st != VGPR_OK) return st;
   Carver cv(static_cast<char*>(ctx->work.ptr) + work_offset);
   uint64_t* keys_a = cv.take<uint64_t>(n);
   uint64_t* keys_b = cv.take<uint64_t>(n);
   uint32_t* vals_tmp = cv.take<uint32_t>(n);
-  uint32_t* hist = cv.take<uint32_t>(256 * (size_t)nblocks);
-  uint32_t* row_total = cv.take<uint32_t>(256);
-  uint32_t* block_sums = cv.take<uint32_t>(nblocks);
-  int* part = cv.take<int>(6 * (size_t)kblocks);
-  int64_t* d_fo = cv.take<int64_t>(nf + 1);
-  unsigned long long* d_res = cv.take<unsigned long long>(res_words);
+  uint32_t* zero = cv.take<uint32_t>(words);
+  KeyPart* part = cv.take<KeyPart>(kblocks);
+  int64_t* d_fo = cv.take<int64_t>((size_t)nf + 1);
+  KeyForm* form = cv.take<KeyForm>(1);
 
   int64_t* h_fo = static_cast<int64_t*>(ctx->pinned);
   unsigned long long* h_res = reinterpret_cast<unsigned long long*>(h_fo + nf + 1);
   std::copy(fo.begin(), fo.end(), h_fo);
-  VGPR_HIP(ctx, hipMemcpyAsync(d_fo, h_fo, sizeof(int64_t) * (nf + 1), hipMemcpyHostToDevice, ctx->stream));
-  VGPR_HIP(ctx, hipMemsetAsync(d_res, 0, sizeof(unsigned long long) * res_words, ctx->stream));
+  std::fill(h_res, h_res + res_words, 0ull);
 
   uint32_t* perm = reinterpret_cast<uint32_t*>(d_perm);
-  KeyForm kf{};
-  kf.B = 0;
-  kf.morton = morton ? 1 : 0;
+  uint32_t* narrow = reinterpret_cast<uint32_t*>(keys_b);  // its two halves, while keys_a has the packed keys
+  auto pass = [&](auto kernel, int threads, uint32_t per_tile, auto* a, auto* b, int p) {
+    hipLaunchKernelGGL(kernel, dim3((n + per_tile - 1) / per_tile), dim3(threads), 0, ctx->stream, a, b, perm, vals_tmp,
+                       n, p, form, d_fo, nf, zero + o_hist, zero + o_status, max_tiles, zero + o_ticket);
+  };
+  auto segment = [&](auto kernel, auto* a, auto* b) {
+    ProfScope ps(ctx, "voxelize_segment");
+    hipLaunchKernelGGL(kernel, dim3(nseg), dim3(small ? kSmallSeg : kLargeSeg), 0, ctx->stream, a, b, n, form, d_fo, nf,
+                       reinterpret_cast<unsigned long long*>(zero), nseg, zero + o_ticket + kMaxPasses, cap_vox, d_keys,
+                       d_offsets, d_counts, h_res);
+  };
   if (n > 0) {
-    const double inv_s = 1.0 / (double)voxel_size;
-    // keys and the batch's index ranges; the ranges decide the sort key's width
     {
       ProfScope ps(ctx, "voxelize_key");
-      hipLaunchKernelGGL(key_kernel, dim3(kblocks), dim3(256), 0, ctx->stream, d_xyz, n, inv_s, keys_a, part,
-                         d_res);
-      hipLaunchKernelGGL(minmax_kernel, dim3(1), dim3(1024), 0, ctx->stream, part, kblocks, d_res);
+      hipLaunchKernelGGL(key_kernel, dim3(kblocks), dim3(kKeyThreads), 0, ctx->stream, d_xyz, n,
+                         1.0 / (double)voxel_size, keys_a, part, zero, zero_words, h_fo, d_fo, nf);
+      auto compose = [&](auto kernel, uint32_t per_block) {
+        hipLaunchKernelGGL(kernel, dim3(std::min<uint32_t>((n + per_block - 1) / per_block, kComposeBlocks)),
+                           dim3(kComposeThreads), 0, ctx->stream, keys_a, narrow, n, part, (int)kblocks, morton ? 1 : 0,
+                           d_fo, nf, form, zero + o_hist);
+      };
+      if (small) compose(compose_kernel<kSmallCompose>, kComposeThreads * kSmallCompose);
+      else compose(compose_kernel<kLargeCompose>, kComposeThreads * kLargeCompose);
     }
-    VGPR_HIP(ctx, hipGetLastError());
-    VGPR_HIP(ctx, hipMemcpyAsync(h_res, d_res, sizeof(unsigned long long) * R_FRAMES, hipMemcpyDeviceToHost,
-                                 ctx->stream));
-    VGPR_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (h_res[R_RANGE]) return fail(ctx, VGPR_E_RANGE, "a point's voxel index is outside +-(2^20 - 1)");
-    auto bits = [](int64_t r) {
-      int b = 0;
-      while (r > 0) {
-        ++b;
-        r >>= 1;
+    {
+      ProfScope ps(ctx, "voxelize_sort");
+      for (int p = 0; p < kNarrowPasses; ++p) {
+        if (small)
+          pass(radix_pass<uint32_t, kSmallThreads, kSmallItems>, kSmallThreads, kSmallThreads * kSmallItems, narrow,
+               narrow + n, p);
+        else
+          pass(radix_pass<uint32_t, kLargeThreads, kLargeItems>, kLargeThreads, kLargeThreads * kLargeItems, narrow,
+               narrow + n, p);
       }
-      return b;
-    };
-    const bool any_valid = (int64_t)h_res[R_INVALID] < n;
-    for (int a = 0; a < 3; ++a) kf.mn[a] = any_valid ? (int64_t)(long long)h_res[R_MIN + a] : 0;
-    const int b3[3] = {any_valid ? bits((int64_t)(long long)h_res[R_MAX + 0] - kf.mn[0]) : 0,
-                       any_valid ? bits((int64_t)(long long)h_res[R_MAX + 1] - kf.mn[1]) : 0,
-                       any_valid ? bits((int64_t)(long long)h_res[R_MAX + 2] - kf.mn[2]) : 0};
-    kf.bx = b3[0];
-    kf.by = b3[1];
-    kf.bz = b3[2];
-    kf.B = kf.bx + kf.by + kf.bz;
-    const int bf = nf > 1 ? bits(nf - 1) : 0;
-    kf.embed = (kf.B + 1 + bf) <= 64 ? 1 : 0;
-    const int key_bits = kf.B + 1 + (kf.embed ? bf : 0);
-    kf.key_passes = (key_bits + 7) / 8;
-    int passes = kf.key_passes;
-    if (!kf.embed && nf > 1) passes += (bf + 7) / 8;
-    // choose index buffers so that the last pass writes them into d_perm:
-    // pass p writes vbuf[(passes - 1 - p) & 1]; the input of pass 0 is the other one
-    uint32_t* vbuf[2] = {perm, vals_tmp};
-    const int first_in = (passes & 1) ? 1 : 0;
-    hipLaunchKernelGGL(compose_kernel, dim3(kblocks), dim3(256), 0, ctx->stream, keys_a, vbuf[first_in], n, kf, d_fo,
-                       nf);
+    }
+    if (small) segment(segment_kernel<uint32_t, kSmallSeg>, narrow, narrow + n);
+    else segment(segment_kernel<uint32_t, kLargeSeg>, narrow, narrow + n);
     VGPR_HIP(ctx, hipGetLastError());
-    int in = first_in;
-    // keys ping-pong separately, starting in keys_a
-    uint64_t* kcur = keys_a;
-    uint64_t* kalt = keys_b;
+  }
+  VGPR_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  if (h_res[R_RANGE]) return fail(ctx, VGPR_E_RANGE, "a point's voxel index is outside +-(2^20 - 1)");
+  const int passes = (int)h_res[R_PASSES];
+  if (passes > kNarrowPasses) {
     {
       ProfScope ps(ctx, "voxelize_sort");
       for (int p = 0; p < passes; ++p) {
-        const int out = in ^ 1;
-        hipLaunchKernelGGL(radix_upsweep, dim3(nblocks), dim3(kSortThreads), 0, ctx->stream, kcur, vbuf[in], n, p,
-                           kf.key_passes, d_fo, nf, hist, nblocks);
-        hipLaunchKernelGGL(radix_rowscan, dim3(256), dim3(1024), 0, ctx->stream, hist, nblocks, row_total);
-        hipLaunchKernelGGL(radix_downsweep, dim3(nblocks), dim3(kSortThreads), 0, ctx->stream, kcur, vbuf[in], kalt,
-                           vbuf[out], n, p, kf.key_passes, d_fo, nf, hist, row_total, nblocks);
-        in = out;
-        uint64_t* t = kcur;
-        kcur = kalt;
-        kalt = t;
+        if (small)
+          pass(radix_pass<uint64_t, kSmallThreads, kSmallItems>, kSmallThreads, kSmallThreads * kSmallItems, keys_a,
+               keys_b, p);
+        else
+          pass(radix_pass<uint64_t, kWideThreads, kWideItems>, kWideThreads, kWideThreads * kWideItems, keys_a, keys_b,
+               p);
       }
     }
+    if (small) segment(segment_kernel<uint64_t, kSmallSeg>, keys_a, keys_b);
+    else segment(segment_kernel<uint64_t, kLargeSeg>, keys_a, keys_b);
     VGPR_HIP(ctx, hipGetLastError());
-    const uint64_t* sorted = kcur;
-    {
-      ProfScope ps(ctx, "voxelize_segment");
-      hipLaunchKernelGGL(seg_reduce, dim3(nblocks), dim3(kSortThreads), 0, ctx->stream, sorted, n, kf, d_fo, nf,
-                         block_sums);
-      hipLaunchKernelGGL(seg_scan_blocks, dim3(1), dim3(1024), 0, ctx->stream, block_sums, nblocks, d_res);
-      hipLaunchKernelGGL(seg_scatter, dim3(nblocks), dim3(kSortThreads), 0, ctx->stream, sorted, n, kf, d_fo, nf,
-                         block_sums, cap_vox, d_keys, d_offsets, d_counts);
-      const int64_t fin = std::max<int64_t>(n, nf + 1);
-      hipLaunchKernelGGL(seg_finish, dim3((unsigned)((fin + 255) / 256)), dim3(256), 0, ctx->stream, d_offsets,
-                         d_counts, cap_vox, d_fo, nf, d_res);
-    }
-    VGPR_HIP(ctx, hipGetLastError());
+    VGPR_HIP(ctx, hipStreamSynchronize(ctx->stream));
   }
-  VGPR_HIP(ctx, hipMemcpyAsync(h_res, d_res, sizeof(unsigned long long) * res_words, hipMemcpyDeviceToHost,
-                               ctx->stream));
-  VGPR_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  if (h_res[R_RANGE]) return fail(ctx, VGPR_E_RANGE, "a point's voxel index is outside +-(2^20 - 1)");
   const int64_t nvox = (int64_t)h_res[R_NVOX];
   *h_n_vox = nvox;
   if (h_n_invalid) *h_n_invalid = (int64_t)h_res[R_INVALID];
