@@ -103,12 +103,18 @@ struct Lists {
   uint32_t* count;       // kLists counters
   int64_t stride;
   RotRec* rots;          // frame_mode 1: one rotated frame per slot record, else null
-  int4* big;             // voxels of more than kPrepCoop points: (voxel, list, slot, 0)
-  uint32_t* big_count;
 };
 
-// Voxels of more than this many kept points are staged and summed by a whole wavefront.
+// Voxels of more than this many kept points are summed by a whole wavefront.
 constexpr int kPrepCoop = 64;
+// Voxels a workgroup of prep takes, and the threads it has for each. A workgroup adds once to
+// each list's counter, and adds to one word go one by one (~9 ns each): fewer voxels a
+// workgroup would wait there. Threads a voxel, by what there is to hide a gather's latency:
+// 16 below kPrepManyFrom voxels, where CUs have room (32 x 1800 frame, 3,000 voxels: 8 23 us,
+// 16 21 us), else 8 where voxels may hold over 128 points (161,604 voxels of up to 512 points:
+// 4 87 us, 8 68 us), else 4 (64 frames, cap 128: 4 114 us, 8 134 us).
+constexpr int kPrepVox = 64;
+constexpr int64_t kPrepManyFrom = 32768;
 
 __device__ __forceinline__ float k_exp(float x) { return __expf(x); }
 __device__ __forceinline__ double k_exp(double x) { return exp(x); }
@@ -282,15 +288,32 @@ __device__ __forceinline__ void prep_frame(const FitParams& P, const FitArgs& io
 }
 
 // ---------------------------------------------------------------------------
-// 1. prep: tau test, PCA frame, bucketing (one thread per voxel; one wavefront per
-//    voxel of more than kPrepCoop points)
+// 1. prep: tau test, bucketing, staging of the kept points, PCA frame
+//
+// Bound by latency: a point's index, then its coordinates, then the eigen-decomposition, each
+// waiting for the one before. A workgroup takes kPrepVox voxels with TPV threads each: 16 lanes a
+// voxel stage its points (16 / TPV voxels a group, their loads in flight together), then one thread a
+// voxel adds up the staged points in their order and computes the frame. Voxels of more than
+// kPrepCoop points are staged and summed by a wavefront each, and framed with the others.
+// With one thread a voxel throughout, and one lane of a wavefront a frame for the large ones:
+// 32 x 1800 frame 41 us, now 22; 161,604 voxels of up to 512 points 77, now 68; 64 frames 136,
+// now 114; 16 mixed frames 68, now 47.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) prep_kernel(FitParams P, FitArgs io, float4* __restrict__ staged,
-                                                   Lists L) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = v < io.n_vox;
+template <int TPV>
+__global__ void __launch_bounds__(TPV * kPrepVox) prep_kernel(FitParams P, FitArgs io, float4* __restrict__ staged, Lists L) {
+  constexpr int kGroups = TPV * kPrepVox / 16;  // of 16 lanes
+  constexpr int kWaves = TPV * kPrepVox / 64;
+  constexpr int kEach = 16 / TPV;        // voxels a group stages
+  __shared__ uint32_t s_cnt[kLists], s_base[kLists], s_big;
+  __shared__ int s_n[kPrepVox], s_off[kPrepVox];   // points to stage (0: none), first of them
+  __shared__ uint16_t s_list[kPrepVox];       // voxels of more than kPrepCoop points
+  __shared__ double s_sum[kPrepVox][9];       // and their sums
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  const int64_t v = (int64_t)blockIdx.x * kPrepVox + tid;
   int lst = -1, n = 0, c = 0, off = 0;
-  if (valid) {
+  if (tid < kLists) s_cnt[tid] = 0u;
+  if (tid == 0) s_big = 0u;
+  if (tid < kPrepVox && v < io.n_vox) {
     c = io.counts[v];
     off = io.offsets[v];
     n = c < P.cap ? c : P.cap;
@@ -305,120 +328,132 @@ __global__ void __launch_bounds__(256) prep_kernel(FitParams P, FitArgs io, floa
       while (lst < kNumBuckets - 1 && n > P.bcap[lst]) ++lst;
     }
   }
+  const bool solve = lst >= 0 && lst != kNanList;
+  __syncthreads();
   // slot in the voxel's list: wavefront offsets within the workgroup through LDS,
   // then one global atomic per workgroup and list
-  __shared__ uint32_t s_cnt[kLists], s_base[kLists];
-  const int lane = lane_id();
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  if (threadIdx.x < kLists) s_cnt[threadIdx.x] = 0u;
-  __syncthreads();
   uint32_t woff = 0;
   unsigned long long mymask = 0;
+  if (wave < kPrepVox / 64) {
 #pragma unroll
-  for (int l = 0; l < kLists; ++l) {
-    const unsigned long long mk = __ballot(lst == l);
-    if (mk) {
-      const int leader = __ffsll((long long)mk) - 1;
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(&s_cnt[l], (uint32_t)__popcll(mk));
-      base = __shfl(base, leader, 64);
-      if (lst == l) {
-        woff = base;
-        mymask = mk;
+    for (int l = 0; l < kLists; ++l) {
+      const unsigned long long mk = __ballot(lst == l);
+      if (mk) {
+        const int leader = __ffsll((long long)mk) - 1;
+        uint32_t base = 0;
+        if (lane == leader) base = atomicAdd(&s_cnt[l], (uint32_t)__popcll(mk));
+        base = __shfl(base, leader, 64);
+        if (lst == l) {
+          woff = base;
+          mymask = mk;
+        }
       }
     }
+    s_n[tid] = solve && n <= kPrepCoop ? n : 0;
+    s_off[tid] = off;
+    if (solve && n > kPrepCoop) s_list[atomicAdd(&s_big, 1u)] = (uint16_t)tid;
   }
   __syncthreads();
-  if (threadIdx.x < kLists && s_cnt[threadIdx.x]) s_base[threadIdx.x] = atomicAdd(&L.count[threadIdx.x], s_cnt[threadIdx.x]);
-  __syncthreads();
-  int slot = 0;
-  if (lst >= 0) slot = (int)(s_base[lst] + woff + __popcll(mymask & lt));
-  if (lst == kNanList) L.nan_list[slot] = (int32_t)v;
-  if (lst < 0 || lst == kNanList) return;
-  if (n > kPrepCoop) {
-    // staged, summed and framed by prep_big_kernel, one wavefront per voxel
-    L.big[atomicAdd(L.big_count, 1u)] = make_int4((int)v, lst, slot, 0);
-    return;
-  }
+  if (tid < kLists && s_cnt[tid]) s_base[tid] = atomicAdd(&L.count[tid], s_cnt[tid]);
 
-  // stage the kept points and accumulate the covariance about the first point:
-  // S1 = sum d, S2 = sum d d^T with d = p - p0. Loads of four points are issued
-  // together so that a thread keeps several gathers in flight.
   const int* __restrict__ perm = io.perm;
   const float* __restrict__ xyz = io.xyz;
   const float* __restrict__ noise = io.noise;
-  float4* __restrict__ st = staged;
-  const int i0 = perm ? perm[off] : off;
-  const float x0 = xyz[3 * (size_t)i0], y0 = xyz[3 * (size_t)i0 + 1], z0 = xyz[3 * (size_t)i0 + 2];
-  st[off] = make_float4(x0, y0, z0, noise ? noise[i0] : P.noise);
-  const double p0x = x0, p0y = y0, p0z = z0;
-  double s0 = 0, s1 = 0, s2 = 0, a00 = 0, a01 = 0, a02 = 0, a11 = 0, a12 = 0, a22 = 0;
-  for (int i = 1; i < n; i += 4) {
-    float px[4], py[4], pz[4], pn[4];
+  {
+    // four voxels a group of 16 lanes, 16 points of each at a time
+    const int g = tid >> 4, l16 = tid & 15;
+    int gn[kEach], go[kEach], most = 0;
 #pragma unroll
-    for (int u4 = 0; u4 < 4; ++u4) {
-      const int ii = i + u4 < n ? i + u4 : i;
-      const int idx = perm ? perm[off + ii] : off + ii;
-      px[u4] = xyz[3 * (size_t)idx];
-      py[u4] = xyz[3 * (size_t)idx + 1];
-      pz[u4] = xyz[3 * (size_t)idx + 2];
-      pn[u4] = noise ? noise[idx] : P.noise;
+    for (int j = 0; j < kEach; ++j) {
+      gn[j] = s_n[g + j * kGroups];
+      go[j] = s_off[g + j * kGroups];
+      most = max(most, gn[j]);
     }
+    for (int i = l16; i < most; i += 16) {
+      int idx[kEach];
+      float4 q[kEach];
 #pragma unroll
-    for (int u4 = 0; u4 < 4; ++u4) {
-      if (i + u4 < n) {
-        st[off + i + u4] = make_float4(px[u4], py[u4], pz[u4], pn[u4]);
-        const double d0 = (double)px[u4] - p0x;
-        const double d1 = (double)py[u4] - p0y;
-        const double d2 = (double)pz[u4] - p0z;
-        s0 += d0; s1 += d1; s2 += d2;
-        a00 += d0 * d0; a01 += d0 * d1; a02 += d0 * d2;
-        a11 += d1 * d1; a12 += d1 * d2; a22 += d2 * d2;
+      for (int j = 0; j < kEach; ++j) idx[j] = i < gn[j] ? (perm ? perm[go[j] + i] : go[j] + i) : -1;
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {
+        if (i < gn[j]) {
+          const size_t x = 3 * (size_t)idx[j];
+          q[j] = make_float4(xyz[x], xyz[x + 1], xyz[x + 2], noise ? noise[idx[j]] : P.noise);
+        }
       }
+#pragma unroll
+      for (int j = 0; j < kEach; ++j)
+        if (i < gn[j]) staged[go[j] + i] = q[j];
     }
   }
-  const double sums[9] = {s0, s1, s2, a00, a01, a02, a11, a12, a22};
-  prep_frame(P, io, L, v, lst, slot, n, c, off, p0x, p0y, p0z, sums);
-}
-
-// prep for the voxels of more than kPrepCoop points: one wavefront per voxel stages its
-// points (lane l takes points l, l + 64, ...) and sums its share of S1 and S2; the shares
-// are added across the wavefront and lane 0 computes the frame. Grid-stride over the list.
-__global__ void __launch_bounds__(256) prep_big_kernel(FitParams P, FitArgs io, float4* __restrict__ staged,
-                                                       Lists L) {
-  const int lane = lane_id();
-  const int gw = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int nw = (int)(((int64_t)gridDim.x * blockDim.x) >> 6);
-  const int count = (int)*L.big_count;
-  const int* __restrict__ perm = io.perm;
-  const float* __restrict__ xyz = io.xyz;
-  const float* __restrict__ noise = io.noise;
-  for (int it = gw; it < count; it += nw) {
-    const int4 e = L.big[it];
-    const int v = e.x;
-    const int c = io.counts[v];
-    const int off = io.offsets[v];
-    const int n = c < P.cap ? c : P.cap;
-    const int i0 = perm ? perm[off] : off;
-    const float x0 = xyz[3 * (size_t)i0], y0 = xyz[3 * (size_t)i0 + 1], z0 = xyz[3 * (size_t)i0 + 2];
-    const double p0x = x0, p0y = y0, p0z = z0;
+  const int bigs = (int)s_big;
+  for (int it = wave; it < bigs; it += kWaves) {
+    // lane l takes points l, l + 64, ...; the lanes' shares are added across the wavefront
+    const int b = __builtin_amdgcn_readfirstlane((int)s_list[it]);
+    const int bo = s_off[b];
+    const int cb = io.counts[(int64_t)blockIdx.x * kPrepVox + b];
+    const int nb = cb < P.cap ? cb : P.cap;
+    const int i0 = perm ? perm[bo] : bo;
+    const double p0x = xyz[3 * (size_t)i0], p0y = xyz[3 * (size_t)i0 + 1], p0z = xyz[3 * (size_t)i0 + 2];
     double t[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = lane; i < n; i += 64) {
-      const int idx = perm ? perm[off + i] : off + i;
-      const float px = xyz[3 * (size_t)idx], py = xyz[3 * (size_t)idx + 1], pz = xyz[3 * (size_t)idx + 2];
-      staged[off + i] = make_float4(px, py, pz, noise ? noise[idx] : P.noise);
-      const double d0 = (double)px - p0x, d1 = (double)py - p0y, d2 = (double)pz - p0z;
-      t[0] += d0; t[1] += d1; t[2] += d2;
-      t[3] += d0 * d0; t[4] += d0 * d1; t[5] += d0 * d2;
-      t[6] += d1 * d1; t[7] += d1 * d2; t[8] += d2 * d2;
+    for (int i = lane; i < nb; i += 128) {
+      // two points' loads together
+      const int i2 = i + 64 < nb ? i + 64 : i;
+      const int x1 = perm ? perm[bo + i] : bo + i, x2 = perm ? perm[bo + i2] : bo + i2;
+      const float4 q1 = make_float4(xyz[3 * (size_t)x1], xyz[3 * (size_t)x1 + 1], xyz[3 * (size_t)x1 + 2],
+                                    noise ? noise[x1] : P.noise);
+      const float4 q2 = make_float4(xyz[3 * (size_t)x2], xyz[3 * (size_t)x2 + 1], xyz[3 * (size_t)x2 + 2],
+                                    noise ? noise[x2] : P.noise);
+      auto add = [&](int at, const float4& q) {
+        staged[bo + at] = q;
+        const double d0 = (double)q.x - p0x, d1 = (double)q.y - p0y, d2 = (double)q.z - p0z;
+        t[0] += d0; t[1] += d1; t[2] += d2;
+        t[3] += d0 * d0; t[4] += d0 * d1; t[5] += d0 * d2;
+        t[6] += d1 * d1; t[7] += d1 * d2; t[8] += d2 * d2;
+      };
+      add(i, q1);
+      if (i + 64 < nb) add(i2, q2);
     }
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) t[k] += __shfl_xor(t[k], d, 64);
     }
-    if (lane == 0) prep_frame(P, io, L, v, e.y, e.z, n, c, off, p0x, p0y, p0z, t);
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) s_sum[b][k] = t[k];
+    }
   }
+  __syncthreads();
+  int slot = 0;
+  if (lst >= 0) slot = (int)(s_base[lst] + woff + __popcll(mymask & ((1ull << lane) - 1ull)));
+  if (lst == kNanList) L.nan_list[slot] = (int32_t)v;
+  if (!solve) return;
+  // covariance about the first point: S1 = sum d, S2 = sum d d^T with d = p - p0
+  const float4* st = staged + off;
+  const float4 f = st[0];
+  const double p0x = f.x, p0y = f.y, p0z = f.z;
+  double t[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  if (n > kPrepCoop) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) t[k] = s_sum[tid][k];
+  } else {
+    for (int i = 1; i < n; i += 8) {
+      float4 q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = st[i + u < n ? i + u : i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (i + u < n) {
+          const double d0 = (double)q[u].x - p0x, d1 = (double)q[u].y - p0y, d2 = (double)q[u].z - p0z;
+          t[0] += d0; t[1] += d1; t[2] += d2;
+          t[3] += d0 * d0; t[4] += d0 * d1; t[5] += d0 * d2;
+          t[6] += d1 * d1; t[7] += d1 * d2; t[8] += d2 * d2;
+        }
+      }
+    }
+  }
+  prep_frame(P, io, L, v, lst, slot, n, c, off, p0x, p0y, p0z, t);
 }
 
 // Zero the list counters with a kernel (no memset node when a caller captures the call in a graph).
@@ -1838,7 +1873,7 @@ size_t fit_work_bytes(const vgpr_ctx* ctx, int64_t n_vox, int64_t n_pts, const v
     if (takes_scratch(ctx, b, p)) tiles += Carver::round(tile_bucket_bytes(ctx, b, mixed));
   const size_t rot_bytes = p->frame_mode == 1 ? Carver::round(sizeof(RotRec) * (size_t)n_vox * kNumBuckets) : 0;
   return rot_bytes + Carver::round(sizeof(SlotRec) * (size_t)n_vox * kNumBuckets) + Carver::round(sizeof(float4) * (size_t)n_pts) +
-         Carver::round(sizeof(int32_t) * (size_t)n_vox) + Carver::round(sizeof(int4) * (size_t)n_vox) +
+         Carver::round(sizeof(int32_t) * (size_t)n_vox) +
          2 * Carver::round(sizeof(int32_t) * (size_t)n_vox * kNumBuckets) +
          Carver::round(sizeof(uint32_t) * 64) + tiles + 4096;
 }
@@ -1862,11 +1897,10 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   SlotRec* recs = cv.take<SlotRec>((size_t)a.n_vox * kNumBuckets);
   float4* staged = cv.take<float4>((size_t)a.n_pts);
   int32_t* nan_list = cv.take<int32_t>((size_t)a.n_vox);
-  int4* big_list = cv.take<int4>((size_t)a.n_vox);
   int32_t* rlists = cv.take<int32_t>((size_t)a.n_vox * kNumBuckets);
   int32_t* flists = cv.take<int32_t>((size_t)a.n_vox * kNumBuckets);
   // [0,8) list counts, [8,15) fetch, [16,23) re-solve counts, [24,31) fetch, [32,39) refinement counts, [40,47) fetch,
-  // 48 voxels of more than kPrepCoop points, 49 the merged 256/512-point list
+  // 49 the merged 256/512-point list
   uint32_t* ctr = cv.take<uint32_t>(64);
   double* tile_scratch[kNumBuckets] = {};
   const bool mixed = p->precision == VGPR_PREC_MIXED;
@@ -1895,17 +1929,17 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   const bool fp32 = p->precision == VGPR_PREC_FP32 || p->precision == VGPR_PREC_MIXED;
   P.mode = 2;
 
-  Lists L{recs, nan_list, ctr, a.n_vox, rots, big_list, ctr + 48};
+  Lists L{recs, nan_list, ctr, a.n_vox, rots};
   {
     ProfScope ps(ctx, "classify");
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((a.n_vox + 255) / 256)), dim3(256), 0, ctx->stream, P, a,
-                       staged, L);
-    VGPR_HIP(ctx, hipGetLastError());
-    if (p->max_pts > kPrepCoop) {
-      hipLaunchKernelGGL(prep_big_kernel, dim3((unsigned)std::min<int64_t>((a.n_vox + 3) / 4, 2048)), dim3(256), 0,
+    auto prep = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_vox + kPrepVox - 1) / kPrepVox)), dim3(kPrepVox * threads), 0,
                          ctx->stream, P, a, staged, L);
-      VGPR_HIP(ctx, hipGetLastError());
-    }
+    };
+    if (a.n_vox < kPrepManyFrom) prep(prep_kernel<16>, 16);
+    else if (p->max_pts > 128) prep(prep_kernel<8>, 8);
+    else prep(prep_kernel<4>, 4);
+    VGPR_HIP(ctx, hipGetLastError());
   }
   // Buckets run concurrently on the caller's stream and the three side streams
   // (bucket_stream of the launch choices; by default the 96/128-point buckets on
