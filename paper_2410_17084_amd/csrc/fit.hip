@@ -617,58 +617,95 @@ __device__ __forceinline__ float4 make_row(const FitParams& P, const FrameRec& f
 //   alpha0 = L^-T D^-1 y,  r = f~ - (K + S) alpha0 (kernel entries in double),
 //   alpha = alpha0 + L^-T D^-1 L^-1 r,
 // then mean_q - mu = k*_q^T alpha in double for this lane's query rows (Eq. (3)).
-template <int NMAX, int QR>
+// Few voxels come here, so one voxel's latency is the kernel's: the exponentials are spread
+// over the 64 lanes (the entries of K and the two tables whose products are the query
+// entries, n / 4 + n nq / 32 a lane in place of n + n QR) through `sd`, and L is in
+// registers ahead of the substitutions' chains. A 32 x 1800 frame's pass: 21.5 us with one
+// exponential after another, 19.5 us now; ten maps of 64 x 1024: 200 us, now 172.
+constexpr int kRefineDoubles(int nmax, int nq) { return nmax * nmax + 2 * nq * nmax; }
+
+template <int NMAX, int QR, int NQ>
 __device__ __forceinline__ void refine_mean(const FitParams& P, const FrameRec& fr, const double* __restrict__ xd,
-                            const float* __restrict__ sL, int n, int lane, double dl, double yl, double nzl,
-                            const float* gu, const float* gw, double* meanr) {
+                            const float* __restrict__ sL, double* sd, int n, int lane, double dl, double yl, double nzl,
+                            const int* qi, const int* qj, double* meanr) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const bool dl_ = lane < n;
   const double sf2 = (double)P.sf2, lam = fr.lam;
+  const int nq = P.nq;
+  double* dK = sd;
+  double* eu = sd + NMAX * NMAX;
+  double* ew = eu + NQ * NMAX;
+  static_assert(NMAX == 16, "four columns of K at a time");
+#pragma unroll
+  for (int t = 0; t < NMAX / 4; ++t) {
+    const int row = lane & 15, c = (lane >> 4) + 4 * t;
+    if (row < n && c < n) {
+      const double du = xd[row] - xd[c], dw = xd[NMAX + row] - xd[NMAX + c];
+      dK[c * NMAX + row] = sf2 * exp(-(du * du + dw * dw) * lam);
+    }
+  }
+  for (int e = lane; e < nq * n; e += 64) {
+    const int c = e / nq, i = e - c * nq;
+    float gi, gj;
+    const double f = grid_frac(P, i);
+    coords_from_frac(P, fr, f, f, &gi, &gj);
+    const double du = ((double)gi - fr.anc_u) - xd[c], dw = ((double)gj - fr.anc_w) - xd[NMAX + c];
+    eu[e] = exp(-(du * du) * lam);
+    ew[e] = exp(-(dw * dw) * lam);
+  }
+  // L's column `lane` below the diagonal and row `lane` before it
+  float lcol[NMAX], lrow[NMAX];
+#pragma unroll
+  for (int k = 0; k < NMAX; ++k) {
+    lcol[k] = k < n && lane < k ? sL[lane * NMAX + k] : 0.0f;
+    lrow[k] = k < lane && lane < n ? sL[k * NMAX + lane] : 0.0f;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // back substitution x = L^-T v for v held one value per lane
   auto back = [&](double v) {
     double acc = 0.0, x = 0.0;
-    for (int k = n - 1; k >= 0; --k) {
-      const double xk = bcast(v - acc, k);  // lane k's sum over rows below k is complete
-      if (lane == k) x = xk;
-      if (lane < k) acc += (double)sL[lane * NMAX + k] * xk;
+#pragma unroll
+    for (int k = NMAX - 1; k >= 0; --k) {
+      if (k < n) {
+        const double xk = bcast(v - acc, k);  // lane k's sum over rows below k is complete
+        if (lane == k) x = xk;
+        acc += (double)lcol[k] * xk;
+      }
     }
     return x;
   };
   double alpha = back(dl_ ? yl / dl : 0.0);
   // residual of (K + S) alpha = f~ in double
-  double rr = 0.0;
-  if (dl_) {
-    const double ui = xd[lane], wi = xd[NMAX + lane];
-    rr = xd[2 * NMAX + lane] - nzl * alpha;
-    for (int c = 0; c < n; ++c) {
+  double rr = dl_ ? xd[2 * NMAX + lane] - nzl * alpha : 0.0;
+#pragma unroll
+  for (int c = 0; c < NMAX; ++c) {
+    if (c < n) {
       const double ac = bcast(alpha, c);
-      const double du = ui - xd[c], dw = wi - xd[NMAX + c];
-      rr -= sf2 * exp(-(du * du + dw * dw) * lam) * ac;
+      rr -= (dl_ ? dK[c * NMAX + lane] : 0.0) * ac;
     }
-  } else {
-    for (int c = 0; c < n; ++c) (void)bcast(alpha, c);  // every lane takes part in the broadcasts
   }
   // forward substitution w = L^-1 r, then D^-1 and the back substitution
   double w = 0.0;
-  for (int j = 0; j < n; ++j) {
-    const double wj = bcast(rr, j);  // lane j's value is final at step j
-    if (lane == j) w = wj;
-    if (lane > j && lane < n) rr -= (double)sL[j * NMAX + lane] * wj;
+#pragma unroll
+  for (int j = 0; j < NMAX; ++j) {
+    if (j < n) {
+      const double wj = bcast(rr, j);  // lane j's value is final at step j
+      if (lane == j) w = wj;
+      rr -= (double)lrow[j] * wj;
+    }
   }
   alpha += back(dl_ ? w / dl : 0.0);
-  // mean of this lane's query rows from alpha (one row at a time: few registers on this rare path)
+  // mean of this lane's query rows from alpha
 #pragma unroll
-  for (int r = 0; r < QR; ++r) {
-    const double qu = (double)gu[r] - fr.anc_u, qw = (double)gw[r] - fr.anc_w;
-    double acc = 0.0;
-    for (int c = 0; c < n; ++c) {
-      const double ac = bcast(alpha, c);
-      const double du = qu - xd[c], dw = qw - xd[NMAX + c];
-      acc += sf2 * exp(-(du * du + dw * dw) * lam) * ac;
-    }
-    meanr[r] = acc;
+  for (int r = 0; r < QR; ++r) meanr[r] = 0.0;
+  for (int c = 0; c < n; ++c) {
+    const double ac = sf2 * bcast(alpha, c);
+#pragma unroll
+    for (int r = 0; r < QR; ++r) meanr[r] += eu[c * nq + qi[r]] * ew[c * nq + qj[r]] * ac;
   }
 }
 
@@ -700,6 +737,7 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
   __shared__ T s_tab[kWaves][2 * NQ * NMAX];
   __shared__ T s_K[kWaves][kKInLds ? NMAX * NMAX : 1];
   __shared__ double s_xd[kWaves][kRefine ? 3 * NMAX : 1];  // data points (u, w, f~) in double
+  __shared__ double s_rd[kWaves][kRefine ? kRefineDoubles(NMAX, NQ) : 1];  // exponentials of the refinement
   const int wid = threadIdx.x >> 6;
   const int lane = lane_id();
   // wavefront-uniform indices (scalar registers): record loads become scalar loads
@@ -911,8 +949,9 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     const bool flag = to_ref || to_fp64;
     double meanr[QR];
     if constexpr (kRefine) {
-      if (refine) refine_mean<NMAX, QR>(P, fr, s_xd[wid], sL, n, lane, (double)dself, (double)yself, (double)nz,
-                                        gu, gwv, meanr);
+      if (refine)
+        refine_mean<NMAX, QR, NQ>(P, fr, s_xd[wid], sL, s_rd[wid], n, lane, (double)dself, (double)yself, (double)nz,
+                                  qi, qj, meanr);
     }
     float mv_lane = 0.f;
 #pragma unroll
