@@ -621,7 +621,7 @@ __device__ __forceinline__ float4 make_row(const FitParams& P, const FrameRec& f
 // over the 64 lanes (the entries of K and the two tables whose products are the query
 // entries, n / 4 + n nq / 32 a lane in place of n + n QR) through `sd`, and L is in
 // registers ahead of the substitutions' chains. A 32 x 1800 frame's pass: 21.5 us with one
-// exponential after another, 19.5 us now; ten maps of 64 x 1024: 200 us, now 172.
+// exponential after another, 17 us now; ten maps of 64 x 1024: 200 us, now 157.
 constexpr int kRefineDoubles(int nmax, int nq) { return nmax * nmax + 2 * nq * nmax; }
 
 template <int NMAX, int QR, int NQ>
@@ -709,8 +709,28 @@ __device__ __forceinline__ void refine_mean(const FitParams& P, const FrameRec& 
   }
 }
 
+// Divisors of up to 33 as a multiplication: e / d = e * of[d] >> 16 for e below 1024 (the
+// excess of of[d] over 65536 / d is below 1, so the product's is below e / 65536 < 1 / d).
+struct Reciprocals {
+  uint32_t of[40];
+};
+constexpr Reciprocals make_reciprocals() {
+  Reciprocals r{};
+  for (uint32_t d = 1; d < 40; ++d) r.of[d] = 65536u / d + 1u;
+  return r;
+}
+__constant__ constexpr Reciprocals kReciprocal = make_reciprocals();
+__device__ __forceinline__ int div_by(int e, uint32_t reciprocal) { return (int)((uint32_t)e * reciprocal >> 16); }
+
 // ---------------------------------------------------------------------------
 // 2a. wave solver: one voxel per wavefront, n <= min(NMAX, 64), m <= 64
+//
+// Bound by vector issue: every step's column is one broadcast and one product a query row and
+// the data row, and few wavefronts are there to fill the gaps. So registers decide: with the
+// elimination unrolled in place and table addresses made anew each voxel the 16-point FP32
+// solver holds 79 / 115 / 163 for 64 / 128 / 256 queries (139 / 167 / 278 before), 6 / 4 / 3
+// wavefronts a SIMD. 64 frames, 64 queries: 432 us, now 204; 161,604 voxels, 256 queries: 331,
+// now 135; FP64, 16 mixed frames: 69, now 40.
 // ---------------------------------------------------------------------------
 template <typename T, int NMAX, int QR, bool REF = false>
 __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, FitArgs io,
@@ -725,6 +745,7 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
                                                                 uint32_t* __restrict__ fcount) {
   constexpr bool kKInLds = NMAX <= 32;       // K from its upper triangle through LDS
   constexpr int kWaves = kWaveThreads / 64;
+  constexpr int kChunk = NMAX == 16 ? 4 : 8;  // columns under one branch (16 points: 2 212 us, 4 204, 16 222)
   constexpr int NQ = QR == 1 ? 8 : (QR == 2 ? 12 : 16);  // largest grid side for QR query rows per lane
   // REF: the FP32 pass over flagged voxels with one FP64 refinement step of alpha, which
   // keeps the float factor in the kernel-matrix region once K has been read. The first
@@ -768,6 +789,7 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     ftj[r] = grid_frac(P, qj[r]);
   }
   const double flane = grid_frac(P, lane < P.nq ? lane : 0);
+  const uint32_t rnq = kReciprocal.of[P.nq];
   for (; it < cnt_items; it += nw) {
     const SlotRec r = rn;
     const float4 pt = pn;
@@ -829,7 +851,7 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int nq = P.nq;
     for (int e = lane; e < nq * n; e += 64) {
-      const int c = e / nq, i = e - c * nq;
+      const int c = div_by(e, rnq), i = e - c * nq;
       const T du = su[NMAX + i] - su[c], dw = sw[NMAX + i] - sw[c];
       tu[e] = k_exp(-(du * du) * lam);
       tw[e] = k_exp(-(dw * dw) * lam);
@@ -839,8 +861,9 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
       T* __restrict__ Kt = s_K[wid];
       const int ne = (n + 1) & ~1;
       const int half = ne >> 1;
+      const uint32_t rne = kReciprocal.of[ne + 1];
       for (int e = lane; e < half * (ne + 1); e += 64) {
-        const int p = e / (ne + 1), k = e - p * (ne + 1);
+        const int p = div_by(e, rne), k = e - p * (ne + 1);
         int r, c;
         if (k < ne - p) {
           r = p;
@@ -861,6 +884,15 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
+    // table rows of this lane's queries, told anew each voxel: the addresses of every column
+    // were kept over the loop otherwise (16 or more registers a query row)
+    int ti[QR], tj[QR];
+#pragma unroll
+    for (int r = 0; r < QR; ++r) {
+      ti[r] = qi[r];
+      tj[r] = qj[r];
+      asm volatile("" : "+v"(ti[r]), "+v"(tj[r]));
+    }
     // rows: A = query rows (q = lane + 64 r < m), B = data row (lanes < n) with its right-hand side fy
     T A[QR][NMAX], B[NMAX];
     T fy = fv;
@@ -868,7 +900,7 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     for (int c = 0; c < NMAX; ++c) {
       if (c < n) {
 #pragma unroll
-        for (int r = 0; r < QR; ++r) A[r][c] = sf2 * tu[c * nq + qi[r]] * tw[c * nq + qj[r]];
+        for (int r = 0; r < QR; ++r) A[r][c] = sf2 * tu[c * nq + ti[r]] * tw[c * nq + tj[r]];
         T kb = 0;
         if constexpr (kKInLds) {
           // only data lanes (lane < n <= NMAX) read, so the index stays inside this wavefront's region
@@ -897,41 +929,92 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
     T minpiv = (T)FLT_MAX, score = 0;
     T dself = 1, yself = 0;  // this lane's pivot d_l and y_l
     T* __restrict__ sL = s_K[wid];  // FP32 pass: column j of the unit factor L at sL[j * NMAX + i]
-    for (int j = 0; j < n; ++j) {
-      const T cjB = B[0];
-      const T d = bcast(cjB, j);
-      const T y = bcast(fy, j);  // y_j = (L^-1 f~)_j, final once step j is reached
-      const T inv = recip(d);
-      const T tB = cjB * inv;
-      if constexpr (kRefine) {
-        if (lane == j) {
-          dself = d;
-          yself = y;
+    if constexpr (NMAX == 16) {
+      // The steps unrolled, each inside the one before: the rows stay in their registers (a
+      // rolled loop shifts them down a column a step, which doubled the registers) and the
+      // broadcast lanes are constants.
+      auto step = [&](auto self, auto at) {
+        constexpr int j = decltype(at)::value;
+        if constexpr (j < NMAX) {
+          if (j < n) {
+            const T cjB = B[j];
+            const T d = bcast(cjB, j);
+            const T y = bcast(fy, j);  // y_j = (L^-1 f~)_j, final once step j is reached
+            const T inv = recip(d);
+            const T tB = cjB * inv;
+            if constexpr (kRefine) {
+              if (lane == j) {
+                dself = d;
+                yself = y;
+              }
+              if (lane > j && lane < n) sL[j * NMAX + lane] = tB;  // K was read from this region before step 0
+            }
+#pragma unroll
+            for (int r = 0; r < QR; ++r) {
+              const T cjA = A[r][j];
+              tA[r] = cjA * inv;
+              var[r] -= tA[r] * cjA;
+              mean[r] += tA[r] * y;
+            }
+            fy -= tB * y;
+            minpiv = d < minpiv ? d : minpiv;
+            score += (y < 0 ? -y : y) * inv;
+#pragma unroll
+            for (int c0 = j + 1; c0 < NMAX; c0 += kChunk) {
+              if (c0 < n) {
+#pragma unroll
+                for (int c = c0; c < c0 + kChunk; ++c) {
+                  if (c < NMAX) {
+                    const T col = bcast(cjB, c);  // lane c holds data row c; past row n-1 the value is unused
+#pragma unroll
+                    for (int r = 0; r < QR; ++r) A[r][c] -= tA[r] * col;
+                    B[c] -= tB * col;
+                  }
+                }
+              }
+            }
+            self(self, std::integral_constant<int, j + 1>{});
+          }
         }
-        if (lane > j && lane < n) sL[j * NMAX + lane] = tB;  // K was read from this region before step 0
-      }
+      };
+      step(step, std::integral_constant<int, 0>{});
+    } else {
+      for (int j = 0; j < n; ++j) {
+        const T cjB = B[0];
+        const T d = bcast(cjB, j);
+        const T y = bcast(fy, j);  // y_j = (L^-1 f~)_j, final once step j is reached
+        const T inv = recip(d);
+        const T tB = cjB * inv;
+        if constexpr (kRefine) {
+          if (lane == j) {
+            dself = d;
+            yself = y;
+          }
+          if (lane > j && lane < n) sL[j * NMAX + lane] = tB;  // K was read from this region before step 0
+        }
 #pragma unroll
-      for (int r = 0; r < QR; ++r) {
-        const T cjA = A[r][0];
-        tA[r] = cjA * inv;
-        var[r] -= tA[r] * cjA;
-        mean[r] += tA[r] * y;
-      }
-      fy -= tB * y;
-      minpiv = d < minpiv ? d : minpiv;
-      score += (y < 0 ? -y : y) * inv;
-      const int Lc = n - j - 1;
+        for (int r = 0; r < QR; ++r) {
+          const T cjA = A[r][0];
+          tA[r] = cjA * inv;
+          var[r] -= tA[r] * cjA;
+          mean[r] += tA[r] * y;
+        }
+        fy -= tB * y;
+        minpiv = d < minpiv ? d : minpiv;
+        score += (y < 0 ? -y : y) * inv;
+        const int Lc = n - j - 1;
 #pragma unroll
-      for (int c0 = 0; c0 < NMAX - 1; c0 += 8) {
-        if (c0 < Lc) {
+        for (int c0 = 0; c0 < NMAX - 1; c0 += kChunk) {
+          if (c0 < Lc) {
 #pragma unroll
-          for (int k = c0; k < c0 + 8; ++k) {
-            if (k < NMAX - 1) {
-              // lane j+1+k holds data row j+1+k; past row n-1 the value is unused
-              const T col = bcast(cjB, (j + 1 + k) & 63);
+            for (int k = c0; k < c0 + kChunk; ++k) {
+              if (k < NMAX - 1) {
+                // lane j+1+k holds data row j+1+k; past row n-1 the value is unused
+                const T col = bcast(cjB, (j + 1 + k) & 63);
 #pragma unroll
-              for (int r = 0; r < QR; ++r) A[r][k] = A[r][k + 1] - tA[r] * col;
-              B[k] = B[k + 1] - tB * col;
+                for (int r = 0; r < QR; ++r) A[r][k] = A[r][k + 1] - tA[r] * col;
+                B[k] = B[k + 1] - tB * col;
+              }
             }
           }
         }
@@ -964,10 +1047,10 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
         mv_lane = fmaxf(mv_lane, failed ? 0.f : vv);
       }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mv_lane = fmaxf(mv_lane, __shfl_xor(mv_lane, d, 64));
+    // the largest variance is only compared with eta
+    const float mv = __ballot(mv_lane > P.eta) ? INFINITY : 0.f;
     if (lane == 0)
-      finish_voxel(P, io, v, slots ? slots[it] : it, cnt, fr.axes, failed, flag, mv_lane, to_ref ? flist : rlist,
+      finish_voxel(P, io, v, slots ? slots[it] : it, cnt, fr.axes, failed, flag, mv, to_ref ? flist : rlist,
                    to_ref ? fcount : rcount, refine);
   }
 }
