@@ -115,6 +115,8 @@ constexpr int kPrepCoop = 64;
 // 4 87 us, 8 68 us), else 4 (64 frames, cap 128: 4 114 us, 8 134 us).
 constexpr int kPrepVox = 64;
 constexpr int64_t kPrepManyFrom = 32768;
+// Buckets are taken longest voxel first from this many voxels on.
+constexpr int64_t kOrderFrom = 8192;
 
 __device__ __forceinline__ float k_exp(float x) { return __expf(x); }
 __device__ __forceinline__ double k_exp(double x) { return exp(x); }
@@ -299,20 +301,29 @@ __device__ __forceinline__ void prep_frame(const FitParams& P, const FitArgs& io
 // 32 x 1800 frame 41 us, now 22; 161,604 voxels of up to 512 points 77, now 68; 64 frames 136,
 // now 114; 16 mixed frames 68, now 47.
 // ---------------------------------------------------------------------------
+// NaN rows of a voxel below tau, written by one wavefront.
+__device__ __forceinline__ void nan_rows(const FitParams& P, float* __restrict__ out, int64_t v, int lane) {
+  const float nan = __int_as_float(0x7fc00000);
+  float4* o = reinterpret_cast<float4*>(out) + (size_t)v * P.m;
+  for (int q = lane; q < P.m; q += 64) o[q] = make_float4(nan, nan, nan, nan);
+}
+
 template <int TPV>
 __global__ void __launch_bounds__(TPV * kPrepVox) prep_kernel(FitParams P, FitArgs io, float4* __restrict__ staged, Lists L) {
   constexpr int kGroups = TPV * kPrepVox / 16;  // of 16 lanes
   constexpr int kWaves = TPV * kPrepVox / 64;
   constexpr int kEach = 16 / TPV;        // voxels a group stages
-  __shared__ uint32_t s_cnt[kLists], s_base[kLists], s_big;
+  constexpr bool kNanRows = TPV == 16;   // rows of voxels below tau are written here, not by nan_kernel
+  __shared__ uint32_t s_cnt[kLists], s_base[kLists], s_big, s_nans;
   __shared__ int s_n[kPrepVox], s_off[kPrepVox];   // points to stage (0: none), first of them
   __shared__ uint16_t s_list[kPrepVox];       // voxels of more than kPrepCoop points
+  __shared__ uint16_t s_nan[kNanRows ? kPrepVox : 1];
   __shared__ double s_sum[kPrepVox][9];       // and their sums
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int64_t v = (int64_t)blockIdx.x * kPrepVox + tid;
   int lst = -1, n = 0, c = 0, off = 0;
   if (tid < kLists) s_cnt[tid] = 0u;
-  if (tid == 0) s_big = 0u;
+  if (tid == 0) s_big = s_nans = 0u;
   if (tid < kPrepVox && v < io.n_vox) {
     c = io.counts[v];
     off = io.offsets[v];
@@ -352,6 +363,7 @@ __global__ void __launch_bounds__(TPV * kPrepVox) prep_kernel(FitParams P, FitAr
     s_n[tid] = solve && n <= kPrepCoop ? n : 0;
     s_off[tid] = off;
     if (solve && n > kPrepCoop) s_list[atomicAdd(&s_big, 1u)] = (uint16_t)tid;
+    if (kNanRows && lst == kNanList) s_nan[atomicAdd(&s_nans, 1u)] = (uint16_t)tid;
   }
   __syncthreads();
   if (tid < kLists && s_cnt[tid]) s_base[tid] = atomicAdd(&L.count[tid], s_cnt[tid]);
@@ -424,10 +436,14 @@ __global__ void __launch_bounds__(TPV * kPrepVox) prep_kernel(FitParams P, FitAr
       for (int k = 0; k < 9; ++k) s_sum[b][k] = t[k];
     }
   }
+  if constexpr (kNanRows) {
+    const int nans = (int)s_nans;
+    for (int it = wave; it < nans; it += kWaves) nan_rows(P, io.out, (int64_t)blockIdx.x * kPrepVox + s_nan[it], lane);
+  }
   __syncthreads();
   int slot = 0;
   if (lst >= 0) slot = (int)(s_base[lst] + woff + __popcll(mymask & ((1ull << lane) - 1ull)));
-  if (lst == kNanList) L.nan_list[slot] = (int32_t)v;
+  if (!kNanRows && lst == kNanList) L.nan_list[slot] = (int32_t)v;
   if (!solve) return;
   // covariance about the first point: S1 = sum d, S2 = sum d d^T with d = p - p0
   const float4* st = staged + off;
@@ -521,12 +537,7 @@ __global__ void __launch_bounds__(256) nan_kernel(FitParams P, float* __restrict
   const int gw = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const int nw = (int)(((int64_t)gridDim.x * blockDim.x) >> 6);
   const int count = (int)L.count[kNanList];
-  const float nan = __int_as_float(0x7fc00000);
-  for (int it = gw; it < count; it += nw) {
-    const int v = L.nan_list[it];
-    float4* o = reinterpret_cast<float4*>(out) + (size_t)v * P.m;
-    for (int q = lane; q < P.m; q += 64) o[q] = make_float4(nan, nan, nan, nan);
-  }
+  for (int it = gw; it < count; it += nw) nan_rows(P, out, L.nan_list[it], lane);
 }
 
 // Status of a solved (or flagged) voxel; lane / thread 0 only.
@@ -2052,13 +2063,14 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   P.mode = 2;
 
   Lists L{recs, nan_list, ctr, a.n_vox, rots};
+  const bool few = a.n_vox < kPrepManyFrom;
   {
     ProfScope ps(ctx, "classify");
     auto prep = [&](auto kernel, int threads) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_vox + kPrepVox - 1) / kPrepVox)), dim3(kPrepVox * threads), 0,
                          ctx->stream, P, a, staged, L);
     };
-    if (a.n_vox < kPrepManyFrom) prep(prep_kernel<16>, 16);
+    if (few) prep(prep_kernel<16>, 16);
     else if (p->max_pts > 128) prep(prep_kernel<8>, 8);
     else prep(prep_kernel<4>, 4);
     VGPR_HIP(ctx, hipGetLastError());
@@ -2084,7 +2096,11 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   bool merge_top = false;  // set below, once the launched buckets are known
   auto runs_fp32 = [&](int b) { return fp32 && b <= tu.fp32_last_bucket && b < first_tile_bucket(ctx); };
   // buckets taken longest voxel first: above 64 points one voxel is long enough to be left over at the end
-  auto ordered = [&](int b) { return b >= 3 ? !runs_fp32(b) : b >= first_tile_bucket(ctx); };
+  // (with few voxels nearly all start at once, and the order costs a launch before the fork)
+  auto ordered = [&](int b) {
+    if (b == kNumBuckets - 1 && merge_top) return true;
+    return a.n_vox >= kOrderFrom && (b >= 3 ? !runs_fp32(b) : b >= first_tile_bucket(ctx));
+  };
   auto launch_b = [&](int b) -> vgpr_status {
     const bool tiled = b >= first_tile_bucket(ctx);
     const bool wave = wave_ok(b) && b <= tu.wave_last_bucket;
@@ -2163,13 +2179,20 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   if (tiles_first)
     for (int b = kNumBuckets - 1; b >= first_tile_bucket(ctx); --b)
       if (launched(b) && !skipped(b) && (st = launch_b(b)) != VGPR_OK) return st;
-  VGPR_HIP(ctx, hipEventRecord(ctx->fork_ev, ctx->stream));
-  for (int i = 0; i < vgpr_ctx::kAux; ++i) VGPR_HIP(ctx, hipStreamWaitEvent(ctx->aux[i], ctx->fork_ev, 0));
+  auto forked = [&](int b) { return launched(b) && !skipped(b) && !(tiles_first && b >= first_tile_bucket(ctx)); };
+  // only side streams that get a bucket fork and join: an event and two waits each
+  bool side[vgpr_ctx::kAux] = {};
+  for (int b = 0; b < kNumBuckets; ++b)
+    for (int i = 0; i < vgpr_ctx::kAux; ++i)
+      if (forked(b) && stream_of(b) == ctx->aux[i]) side[i] = true;
+  if (std::any_of(side, side + vgpr_ctx::kAux, [](bool x) { return x; }))
+    VGPR_HIP(ctx, hipEventRecord(ctx->fork_ev, ctx->stream));
+  for (int i = 0; i < vgpr_ctx::kAux; ++i)
+    if (side[i]) VGPR_HIP(ctx, hipStreamWaitEvent(ctx->aux[i], ctx->fork_ev, 0));
   for (int b = kNumBuckets - 1; b >= 0; --b) {
-    if (!launched(b) || skipped(b) || (tiles_first && b >= first_tile_bucket(ctx))) continue;
-    if ((st = launch_b(b)) != VGPR_OK) return st;
+    if (forked(b) && (st = launch_b(b)) != VGPR_OK) return st;
   }
-  {
+  if (!few) {
     // NaN rows of the voxels below tau: HBM writes only, queued behind the caller's stream's
     // buckets so that they overlap the long solves instead of delaying the fork
     ProfScope ps(ctx, "nan_rows");
@@ -2178,6 +2201,7 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
     VGPR_HIP(ctx, hipGetLastError());
   }
   for (int i = 0; i < vgpr_ctx::kAux; ++i) {
+    if (!side[i]) continue;
     VGPR_HIP(ctx, hipEventRecord(ctx->join_ev[i], ctx->aux[i]));
     VGPR_HIP(ctx, hipStreamWaitEvent(ctx->stream, ctx->join_ev[i], 0));
   }
