@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(256) compact_kernel(const float4* __restrict__
 // table (cell key -> (key, first Gaussian, count) in one 16-byte slot, so that
 // a lookup touches one cache line) behind an occupancy filter: one bit per
 // hash value, set for every occupied cell, at least 64 bits per cell, so that
-// most empty cells of a ring are rejected by one load from a small array.
+// most empty cells of a ring are rejected by one load a column from a small array.
 __global__ void __launch_bounds__(256) gather_kernel(const float* __restrict__ cen, const float* __restrict__ sb,
                                                      const int32_t* __restrict__ orig,
                                                      const int32_t* __restrict__ perm, int64_t nvalid,
@@ -170,6 +170,10 @@ __global__ void __launch_bounds__(256) gather_kernel(const float* __restrict__ c
   G[i] = make_float4(cen[3 * (size_t)k], cen[3 * (size_t)k + 1], cen[3 * (size_t)k + 2], sb[k]);
   gi[i] = orig[k];
 }
+
+// Filter word of 32 consecutive cells along z (the low bits of a cell's key are its z): a
+// point asks one or two words for each column of cells around it, not one a cell.
+__device__ __forceinline__ uint64_t filter_word(uint64_t chunk, int fshift) { return mix64(chunk) >> fshift; }
 
 struct alignas(16) Slot {
   uint64_t key;  // cell key, or the sentinel for an empty slot
@@ -185,8 +189,7 @@ __global__ void __launch_bounds__(256) table_kernel(const uint64_t* __restrict__
   if (c >= nc) return;
   const uint64_t key = ckeys[c];
   const uint64_t hk = mix64(key);
-  const uint64_t fi = hk >> fshift;  // top bits: independent of the slot's low bits
-  atomicOr(&filter[fi >> 5], 1u << (fi & 31));
+  atomicOr(&filter[filter_word(key >> 5, fshift)], 1u << (key & 31));
   int64_t s = (int64_t)(hk & (uint64_t)(nslots - 1));
   for (int64_t probe = 0; probe < nslots; ++probe) {
     const unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long*>(&table[s].key),
@@ -231,114 +234,222 @@ struct Grid {
 // Ring search, kGroup lanes per point: the lanes of a group share out the cells
 // of each ring, then combine their minima with a butterfly of shuffles (the
 // (value, index) order is total, so the result does not depend on who visited
-// what). A group stops once its bound clears; the wavefront runs until every
-// group has stopped, so every lane takes part in the shuffles.
+// what). The cube of radius 1 settles most points; the others go to a list, so
+// that the next rings run on full wavefronts of them.
+//
+// Bound: each visited cell's chain of dependent loads (filter, table, Gaussians), and the adds
+// to a list's counter, which go one by one (~9 ns each): the list is kept in kSegments parts
+// with a counter each. 981,436 points against 1.19M Gaussians, of which 6.5% are left by the
+// first pass: all rings in one kernel, a filter bit a cell 601 us; this pass 393 and the next
+// rings 121 (410 with the parts' points not shared out evenly).
 constexpr int kGroup = 16;
-static_assert(((2 * kRingMax + 1) * (2 * kRingMax + 1) * (2 * kRingMax + 1) + kGroup - 1) / kGroup <= 64,
-              "a lane's cells of one ring must fit the 64-bit hit mask");
+static_assert((((2 * kRingMax + 1) * (2 * kRingMax + 1) + kGroup - 1) / kGroup) * (2 * kRingMax + 1) <= 32,
+              "a lane's cells of one ring must fit the 32-bit hit mask");
 
-constexpr int kQueryThreads = 64;  // four points a workgroup: measured faster than 256-thread workgroups
+constexpr int kQueryThreads = 64;   // four points a workgroup: measured faster than 256-thread workgroups
+constexpr int kSegments = 256;      // parts of the open list, each of a run of consecutive points
+constexpr int kSegmentStride = 16;  // words between their counters: a cache line each
+constexpr int kRingThreads = 256;
+constexpr int kRingBlocks = 2048;
 
-__global__ void __launch_bounds__(kQueryThreads) query_kernel(const float* __restrict__ pts, int64_t n, Grid g, int has_cand,
-                                                    float* __restrict__ val, int32_t* __restrict__ arg,
-                                                    int32_t* __restrict__ fb, uint32_t* __restrict__ fb_n,
-                                                    unsigned long long* __restrict__ bbest) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+struct Point {
+  float x, y, z;
+  double kx, ky, kz;  // its cell
+};
+
+__device__ __forceinline__ Point point_at(const float* __restrict__ pts, int64_t i, const Grid& g) {
+  Point p;
+  p.x = pts[3 * (size_t)i];
+  p.y = pts[3 * (size_t)i + 1];
+  p.z = pts[3 * (size_t)i + 2];
+  p.kx = floor(__dmul_rn((double)p.x, g.inv_h));
+  p.ky = floor(__dmul_rn((double)p.y, g.inv_h));
+  p.kz = floor(__dmul_rn((double)p.z, g.inv_h));
+  return p;
+}
+
+// This lane's share of the shell of radius R: cells of the (2R+1)^3 cube with Chebyshev
+// distance R (all 27 cells for R = 1). First every column's filter words (independent, so
+// they overlap) into a mask of possibly occupied cells, then the table and the Gaussians of
+// those cells only. For R = 1 every lane of the point's group takes part.
+template <int R>
+__device__ __forceinline__ void visit_ring(const Point& p, int gl, const Grid& g, float* best, int* bk) {
+  constexpr int kSide = 2 * R + 1;
+  // cells beyond the key range hold nothing, and clamping keeps them beyond it
+  constexpr double kFar = (double)kKeyAxisLimit + 8.0;
+  const int ix = (int)fmin(fmax(p.kx, -kFar), kFar), iy = (int)fmin(fmax(p.ky, -kFar), kFar),
+            iz = (int)fmin(fmax(p.kz, -kFar), kFar);
+  constexpr int kCols = kSide * kSide, kEach = (kCols + kGroup - 1) / kGroup;
+  const int lim = (int)kKeyAxisLimit, bias = (int)kKeyBias;
+  const int zlo = max(iz - R, -lim), zhi = min(iz + R, lim);
+  auto key_at = [&](int cx, int cy, int cz) {
+    return ((uint64_t)(uint32_t)(cx + bias) << (2 * kKeyFieldBits)) | ((uint64_t)(uint32_t)(cy + bias) << kKeyFieldBits) |
+           (uint64_t)(uint32_t)(cz + bias);
+  };
+  uint32_t hits = 0;  // bit kSide i + b: cell b of column gl + kGroup i may hold Gaussians
+#pragma unroll
+  for (int i = 0; i < kEach; ++i) {
+    const int t = gl + kGroup * i;
+    const int dy = t % kSide - R, dx = t / kSide - R;
+    const int cx = ix + dx, cy = iy + dy;
+    if (t < kCols && abs(cx) <= lim && abs(cy) <= lim && zlo <= zhi) {
+      const uint64_t key = key_at(cx, cy, zlo);
+      const int at = (int)(key & 31);
+      uint64_t word = g.filter[filter_word(key >> 5, g.fshift)];
+      if (at + (zhi - zlo) > 31) word |= (uint64_t)g.filter[filter_word((key >> 5) + 1, g.fshift)] << 32;
+      uint32_t b = (uint32_t)(word >> at) & ((2u << (zhi - zlo)) - 1u);
+      b <<= zlo - (iz - R);
+      if (R > 1 && max(abs(dx), abs(dy)) < R) b &= 1u | (1u << (2 * R));  // inside the shell: its two ends
+      hits |= b << (kSide * i);
+    }
+  }
+  auto visit = [&](int col, int b) {
+    const uint64_t key = key_at(ix + col / kSide - R, iy + col % kSide - R, iz - R + b);
+    int off, cnt;
+    if (!lookup(g.table, g.nslots, key, mix64(key), &off, &cnt)) return;
+    for (int j = off; j < off + cnt; ++j) take_min(gauss_value(p.x, p.y, p.z, g.G[j]), g.gi[j], best, bk);
+  };
+  if constexpr (R == 1) {
+    // nine lanes hold the 27 cells: deal them out to all 16
+    uint32_t all = gl < kCols ? hits << (kSide * gl) : 0u;
+#pragma unroll
+    for (int o = 1; o < kGroup; o <<= 1) all |= (uint32_t)__shfl_xor((int)all, o, 64);
+    for (int c = gl; c < kSide * kCols; c += kGroup)
+      if (all >> c & 1u) visit(c / kSide, c % kSide);
+  } else {
+    while (hits) {
+      const int c = __builtin_ctz(hits);
+      hits &= hits - 1;
+      visit(gl + kGroup * (c / kSide), c % kSide);
+    }
+  }
+}
+
+// The group's minimum in all of its lanes; every lane of the wavefront takes part.
+__device__ __forceinline__ void group_min(float* best, int* bk) {
+#pragma unroll
+  for (int o = 1; o < kGroup; o <<= 1) {
+    const float ov = __shfl_xor(*best, o, 64);
+    const int ok = __shfl_xor(*bk, o, 64);
+    take_min(ov, ok, best, bk);
+  }
+}
+
+// Whether no Gaussian outside the visited cube of radius r can win.
+__device__ __forceinline__ bool settled(const Point& p, int r, const Grid& g, double smax, float best, int bk) {
+  // distance from the point to the faces of the visited cube of cells
+  const double lo = (double)r, hi = (double)(r + 1);
+  double lb = (double)p.x - (p.kx - lo) * g.h;
+  lb = fmin(lb, (p.kx + hi) * g.h - (double)p.x);
+  lb = fmin(lb, (double)p.y - (p.ky - lo) * g.h);
+  lb = fmin(lb, (p.ky + hi) * g.h - (double)p.y);
+  lb = fmin(lb, (double)p.z - (p.kz - lo) * g.h);
+  lb = fmin(lb, (p.kz + hi) * g.h - (double)p.z);
+  // margin: float rounding of the values compared (a few ulps of the distances and scales involved)
+  const double margin = 1e-5 * (fabs(lb) + fabs(smax) + fabs((double)best)) + 1e-7 * g.h;
+  return bk != INT_MAX && lb - smax > (double)best + margin;
+}
+
+// The cube of radius 1 of every point. An open point's best so far stays in its value and
+// index (INT_MAX: none), where the next passes read it.
+__global__ void __launch_bounds__(kQueryThreads) query_kernel(const float* __restrict__ pts, int64_t n, Grid g,
+                                                              int has_cand, float* __restrict__ val,
+                                                              int32_t* __restrict__ arg, int32_t* __restrict__ open,
+                                                              int64_t segment, uint32_t* __restrict__ open_n) {
+  const int64_t i = ((int64_t)blockIdx.x * kQueryThreads + threadIdx.x) / kGroup;
   const int gl = threadIdx.x & (kGroup - 1);
-  float x = 0.f, y = 0.f, z = 0.f;
+  Point p{};
   bool live = false;
   if (i < n) {
-    x = pts[3 * (size_t)i];
-    y = pts[3 * (size_t)i + 1];
-    z = pts[3 * (size_t)i + 2];
-    const bool fin = isfinite(x) && isfinite(y) && isfinite(z);
-    if (gl == 0 && !fin) {
+    p = point_at(pts, i, g);
+    live = isfinite(p.x) && isfinite(p.y) && isfinite(p.z);
+    if (gl == 0 && !live) {
       val[i] = __int_as_float(0x7fc00000);
       arg[i] = -1;
     } else if (gl == 0 && !has_cand) {
       val[i] = INFINITY;
       arg[i] = -1;
     }
-    live = fin && has_cand;
+    live = live && has_cand;
   }
   const double smax = has_cand ? (double)float_unorder(*g.smax) : 0.0;
-  const double kx = floor(__dmul_rn((double)x, g.inv_h));
-  const double ky = floor(__dmul_rn((double)y, g.inv_h));
-  const double kz = floor(__dmul_rn((double)z, g.inv_h));
-  const double lim = (double)kKeyAxisLimit;
   float best = INFINITY;
   int bk = INT_MAX;
-  bool done = !live;
-  // the first pass takes the whole cube of radius 1 (rings 0 and 1 together: a point's own
-  // cell alone almost never settles it), later passes one shell each
-  for (int r = 1; r <= kRingMax; ++r) {
-    if (!done) {
-      // the shell of radius r: cells of the (2r+1)^3 cube with Chebyshev distance r (all 27
-      // cells for r = 1). The
-      // lane's cells t = gl + kGroup i go in two passes: first every filter load (independent,
-      // so they overlap) into a mask of possibly occupied cells, then the table and the
-      // Gaussians of those cells only.
-      const int side = 2 * r + 1, nt = side * side * side;
-      auto cell_key = [&](int t, bool* ok) {
-        const int dz = t % side - r, dy = (t / side) % side - r, dx = t / (side * side) - r;
-        const double cx = kx + dx, cy = ky + dy, cz = kz + dz;
-        const int cheb = max(max(abs(dx), abs(dy)), abs(dz));
-        *ok = (cheb == r || r == 1) && fabs(cx) <= lim && fabs(cy) <= lim && fabs(cz) <= lim;
-        return *ok ? ((uint64_t)((int64_t)cx + kKeyBias) << (2 * kKeyFieldBits)) |
-                         ((uint64_t)((int64_t)cy + kKeyBias) << kKeyFieldBits) | (uint64_t)((int64_t)cz + kKeyBias)
-                   : 0ull;
-      };
-      uint64_t hits = 0;  // bit i: cell gl + kGroup i passed the filter (at most 43 cells a lane for r <= 3)
-#pragma unroll 4
-      for (int i = 0; gl + kGroup * i < nt; ++i) {
-        bool ok;
-        const uint64_t key = cell_key(gl + kGroup * i, &ok);
-        const uint64_t fi = mix64(key) >> g.fshift;  // in range for any key
-        const uint32_t word = g.filter[fi >> 5];
-        if (ok && ((word >> (fi & 31)) & 1u)) hits |= 1ull << i;
-      }
-      while (hits) {
-        const int i = __builtin_ctzll(hits);
-        hits &= hits - 1;
-        bool ok;
-        const uint64_t key = cell_key(gl + kGroup * i, &ok);
-        int off, cnt;
-        if (!lookup(g.table, g.nslots, key, mix64(key), &off, &cnt)) continue;
-        for (int j = off; j < off + cnt; ++j) take_min(gauss_value(x, y, z, g.G[j]), g.gi[j], &best, &bk);
-      }
-    }
-#pragma unroll
-    for (int o = 1; o < kGroup; o <<= 1) {
-      const float ov = __shfl_xor(best, o, 64);
-      const int ok = __shfl_xor(bk, o, 64);
-      take_min(ov, ok, &best, &bk);
-    }
-    if (!done) {
-      // distance from the point to the faces of the visited cube of cells
-      const double lo = (double)r, hi = (double)(r + 1);
-      double lb = (double)x - (kx - lo) * g.h;
-      lb = fmin(lb, (kx + hi) * g.h - (double)x);
-      lb = fmin(lb, (double)y - (ky - lo) * g.h);
-      lb = fmin(lb, (ky + hi) * g.h - (double)y);
-      lb = fmin(lb, (double)z - (kz - lo) * g.h);
-      lb = fmin(lb, (kz + hi) * g.h - (double)z);
-      // margin: float rounding of the values compared (a few ulps of the distances and scales involved)
-      const double margin = 1e-5 * (fabs(lb) + fabs(smax) + fabs((double)best)) + 1e-7 * g.h;
-      if (bk != INT_MAX && lb - smax > (double)best + margin) {
-        done = true;
-        if (gl == 0) {
-          val[i] = best;
-          arg[i] = bk;
-        }
-      }
-    }
-    if (__ballot(!done) == 0ull) break;
+  if (live) visit_ring<1>(p, gl, g, &best, &bk);
+  group_min(&best, &bk);
+  const bool mine = live && gl == 0;
+  if (mine) {
+    val[i] = best;
+    arg[i] = bk;
   }
-  if (!done && gl == 0) {  // still open after kRingMax rings: the brute-force pass resolves it,
-    // starting from the best value the rings found
-    const uint32_t slot = atomicAdd(fb_n, 1u);
-    fb[slot] = (int32_t)i;
-    bbest[slot] = bk == INT_MAX ? ~0ull : pack_best(best, bk);
+  const bool left = mine && !settled(p, 1, g, smax, best, bk);
+  const unsigned long long mask = __ballot(left);
+  if (mask) {
+    // a workgroup's points are of one part: its length is a multiple of their number
+    const int64_t s = (int64_t)blockIdx.x * (kQueryThreads / kGroup) / segment;
+    uint32_t at = 0;
+    if (lane_id() == 0) at = atomicAdd(&open_n[s * kSegmentStride], (uint32_t)__popcll(mask));
+    at = __shfl(at, 0, 64) + (uint32_t)__popcll(mask & ((1ull << lane_id()) - 1ull));
+    if (left) open[s * segment + at] = (int32_t)i;
+  }
+}
+
+// The shells of radius 2 and 3 of the points that the first pass left open; what they leave
+// goes to one list for the brute-force pass.
+__global__ void __launch_bounds__(kRingThreads) ring_kernel(const float* __restrict__ pts, Grid g,
+                                                            float* __restrict__ val, int32_t* __restrict__ arg,
+                                                            const int32_t* __restrict__ open, int64_t segment,
+                                                            const uint32_t* __restrict__ open_n,
+                                                            int32_t* __restrict__ fb, uint32_t* __restrict__ fb_n) {
+  static_assert(kRingMax == 3, "radii 2 and 3");
+  constexpr uint32_t kPoints = kRingThreads / kGroup;
+  __shared__ uint32_t s_n, s_base;
+  __shared__ uint32_t s_end[kSegments], s_scan[kRingThreads / 64 + 1];
+  static_assert(kSegments == kRingThreads, "a thread a part");
+  // open points are bunched (far from the map): all parts as one list, shared out evenly
+  uint32_t count;
+  const uint32_t len = open_n[threadIdx.x * kSegmentStride];
+  s_end[threadIdx.x] = block_exclusive_sum<kRingThreads>(len, s_scan, &count) + len;
+  __syncthreads();
+  const int gl = threadIdx.x & (kGroup - 1);
+  const double smax = (double)float_unorder(*g.smax);
+  for (uint32_t base = blockIdx.x * kPoints; base < count; base += gridDim.x * kPoints) {
+    if (threadIdx.x == 0) s_n = 0u;
+    const uint32_t at = base + threadIdx.x / kGroup;
+    int s = 0;  // first part that ends beyond `at`
+#pragma unroll
+    for (int h = kSegments / 2; h > 0; h >>= 1)
+      if (s_end[s + h - 1] <= at) s += h;
+    int32_t i = -1;
+    Point p{};
+    float best = INFINITY;
+    int bk = INT_MAX;
+    if (at < count) {
+      i = open[s * segment + (at - (s ? s_end[s - 1] : 0u))];
+      p = point_at(pts, i, g);
+      best = val[i];
+      bk = arg[i];
+      visit_ring<2>(p, gl, g, &best, &bk);
+    }
+    group_min(&best, &bk);
+    bool left = i >= 0 && !settled(p, 2, g, smax, best, bk);
+    if (__ballot(left)) {
+      if (left) visit_ring<3>(p, gl, g, &best, &bk);
+      group_min(&best, &bk);
+      left = left && !settled(p, 3, g, smax, best, bk);
+    }
+    if (i >= 0 && gl == 0) {
+      val[i] = best;
+      arg[i] = bk;
+    }
+    __syncthreads();
+    uint32_t slot = 0;
+    if (left && gl == 0) slot = atomicAdd(&s_n, 1u);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) s_base = atomicAdd(fb_n, s_n);
+    __syncthreads();
+    if (left && gl == 0) fb[s_base + slot] = i;
+    __syncthreads();
   }
 }
 
@@ -414,14 +525,14 @@ __global__ void __launch_bounds__(256) nearest_kernel(const float* __restrict__ 
                                                       uint32_t n_open, const float4* __restrict__ G,
                                                       const int32_t* __restrict__ gi, int64_t nvalid,
                                                       const float4* __restrict__ box, int nchunk,
-                                                      const unsigned long long* __restrict__ seed,
                                                       float* __restrict__ val, int32_t* __restrict__ arg) {
   const uint32_t o = (uint32_t)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   if (o >= n_open) return;  // whole wavefronts: o is uniform in a wavefront
   const int lane = lane_id();
   const int i = fb[o];
   const float x = pts[3 * (size_t)i], y = pts[3 * (size_t)i + 1], z = pts[3 * (size_t)i + 2];
-  unsigned long long cur = seed[o];
+  // the rings' best
+  unsigned long long cur = arg[i] == INT_MAX ? ~0ull : pack_best(val[i], arg[i]);
   unsigned long long next = 0;  // smallest (bound, chunk) key a round may still take
   for (;;) {
     // box bounds in float: their rounding (a few ulps of the distance) is far inside the margin,
@@ -555,7 +666,8 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
   const size_t o_cen = sub(12 * (size_t)ng + 16), o_sb = sub(4 * (size_t)ng + 16), o_ck = sub(8 * (size_t)ng + 16),
                o_co = sub(4 * (size_t)ng + 16), o_cc = sub(4 * (size_t)ng + 16), o_pm = sub(4 * (size_t)ng + 16),
                o_G = sub(16 * (size_t)ng + 16), o_gi = sub(4 * (size_t)ng + 16), o_or = sub(4 * (size_t)ng + 16),
-               o_tb = sub(sizeof(Slot) * (size_t)ns), o_fl = sub(16 * (size_t)ng + 64), o_fb = sub(4 * (size_t)n), o_bb = sub(8 * (size_t)n),
+               o_tb = sub(sizeof(Slot) * (size_t)ns), o_fl = sub(16 * (size_t)ng + 64), o_fb = sub(4 * (size_t)n), o_op = sub(4 * ((size_t)n + 8 * kSegments)),
+               o_on = sub(4 * kSegments * kSegmentStride),
                o_box = sub(32 * (size_t)((ng + kBruteChunk - 1) / kBruteChunk) + 32),
                o_bmax = sub(4 * (size_t)((ng + 255) / 256) + 16), o_bc = sub(4 * (size_t)((ng + 255) / 256) + 16),
                o_bo = sub(4 * (size_t)((ng + 255) / 256) + 16),
@@ -580,7 +692,8 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
   Slot* table = reinterpret_cast<Slot*>(w + o_tb);
   uint32_t* filter = reinterpret_cast<uint32_t*>(w + o_fl);
   int32_t* fb = reinterpret_cast<int32_t*>(w + o_fb);
-  unsigned long long* bbest = reinterpret_cast<unsigned long long*>(w + o_bb);
+  int32_t* open = reinterpret_cast<int32_t*>(w + o_op);
+  uint32_t* open_n = reinterpret_cast<uint32_t*>(w + o_on);
   float4* cbox = reinterpret_cast<float4*>(w + o_box);
   uint32_t* bmax = reinterpret_cast<uint32_t*>(w + o_bmax);
   uint32_t* bcnt = reinterpret_cast<uint32_t*>(w + o_bc);
@@ -594,6 +707,7 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
   double* dsum = reinterpret_cast<double*>(w + o_misc + 16);
 
   VGPR_HIP(ctx, hipMemsetAsync(misc, 0, 64, ctx->stream));
+  VGPR_HIP(ctx, hipMemsetAsync(open_n, 0, sizeof(uint32_t) * kSegments * kSegmentStride, ctx->stream));
   int64_t nc = 0, n_bad = 0, n_cand = 0;
   if (ng > 0) {
     // candidates only (rows of unsolved voxels are NaN) go to the voxelizer
@@ -630,15 +744,21 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
     hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((nvalid + 255) / 256)), dim3(256), 0, ctx->stream, cen, sb,
                        orig, perm, nvalid, G, gi);
     hipLaunchKernelGGL(table_kernel, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, ctx->stream, ckeys, coff, ccnt,
-                       nc, table, nsl, filter, 64 - lf);
+                       nc, table, nsl, filter, 64 - (lf - 5));
     VGPR_HIP(ctx, hipGetLastError());
   }
   const double inv_h = 1.0 / (double)cell_size;
-  Grid grid{G, gi, table, nsl, filter, 64 - lf, inv_h, (double)cell_size, misc};
+  Grid grid{G, gi, table, nsl, filter, 64 - (lf - 5), inv_h, (double)cell_size, misc};
   {
     ProfScope ps(ctx, "structure_loss");
-    hipLaunchKernelGGL(query_kernel, dim3((unsigned)((n * kGroup + kQueryThreads - 1) / kQueryThreads)), dim3(kQueryThreads), 0, ctx->stream, d_pts, n, grid,
-                       has_cand ? 1 : 0, val, arg, fb, misc + 1, bbest);
+    // points a part of the open list, a multiple of a query workgroup's
+    constexpr int64_t kPer = kQueryThreads / kGroup;
+    const int64_t segment = ((n + kSegments - 1) / kSegments + kPer - 1) / kPer * kPer;
+    hipLaunchKernelGGL(query_kernel, dim3((unsigned)((n + kPer - 1) / kPer)), dim3(kQueryThreads), 0, ctx->stream, d_pts,
+                       n, grid, has_cand ? 1 : 0, val, arg, open, segment, open_n);
+    if (has_cand)
+      hipLaunchKernelGGL(ring_kernel, dim3(kRingBlocks), dim3(kRingThreads), 0, ctx->stream, d_pts, grid, val,
+                         arg, open, segment, open_n, fb, misc + 1);
     VGPR_HIP(ctx, hipGetLastError());
   }
   // the voxelizer may have grown the pinned staging area: take its address only now
@@ -651,7 +771,7 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
     const unsigned gx = (unsigned)((nvalid + kBruteChunk - 1) / kBruteChunk);
     hipLaunchKernelGGL(chunk_box_kernel, dim3(gx), dim3(256), 0, ctx->stream, G, nvalid, cbox);
     hipLaunchKernelGGL(nearest_kernel, dim3((unsigned)(((int64_t)n_open * 64 + 255) / 256)), dim3(256), 0,
-                       ctx->stream, d_pts, fb, n_open, G, gi, nvalid, cbox, (int)gx, bbest, val, arg);
+                       ctx->stream, d_pts, fb, n_open, G, gi, nvalid, cbox, (int)gx, val, arg);
     VGPR_HIP(ctx, hipGetLastError());
   }
   hipLaunchKernelGGL(sum_tiles, dim3((unsigned)nt), dim3(256), 0, ctx->stream, val, d_pts, n, tsum, tcnt);
