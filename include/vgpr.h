@@ -230,8 +230,8 @@ VGPR_API vgpr_status vgpr_fit_predict(vgpr_ctx* ctx, const float* d_xyz, int64_t
  * itself allocates nothing (no hipMalloc / hipFree, no stream or event
  * creation: the context made its side streams at vgpr_create). The caller
  * still owns every input and output buffer.
- * Limit: the call's scratch (about 525 bytes per voxel + 16 bytes per point,
- * plus the tiled solvers' areas when max_pts > 128 or in MIXED mode) must fit
+ * Limit: the call's scratch (about 510 bytes per voxel + 16 bytes per point,
+ * plus the larger solvers' areas when max_pts > 128 or in MIXED mode) must fit
  * in the 64 MiB; otherwise it returns VGPR_E_CAPACITY and enqueues nothing.
  * Concurrency: every call on one GPU (from any context) shares that GPU's
  * array, which keeps the last call's contents; calls whose work overlaps on
@@ -254,8 +254,8 @@ VGPR_API vgpr_status vgpr_fit_predict_noalloc(vgpr_ctx* ctx, const float* d_xyz,
  * updates' solves run from a staging area that the context holds and its
  * maps share, grown to the largest update so far: the re-solved voxels'
  * stored points back to back (28 bytes per point with the solver's copy),
- * about 530 bytes per re-solved voxel, and the tiled solvers' fixed scratch
- * when max_pts > 64. An update's scratch therefore scales with the voxels it
+ * about 510 bytes per re-solved voxel, and the larger solvers' fixed scratch
+ * when max_pts > 128 (MIXED mode: above 64). An update's scratch therefore scales with the voxels it
  * re-solves, not with max_voxels.
  */
 VGPR_API vgpr_status vgpr_map_create(vgpr_ctx* ctx, const vgpr_params* params, int64_t max_voxels,
@@ -416,33 +416,33 @@ VGPR_API vgpr_status vgpr_graph_destroy(vgpr_graph* graph);
  * change only timing (results are bit-identical); fp32_last_bucket and wave_last_bucket
  * change the rounding (which arithmetic and which solver a voxel gets), and
  * every choice stays within the stated tolerances. Buckets hold voxels of up to
- * 16, 32, 64, 96, 128, 256 and 512 kept points (index 0..6); buckets from
- * tile_first_bucket on run the tiled FP64 solver. Defaults come from the project's
- * autotuner on the spinning-scan workload.
+ * 16, 32, 64, 96, 128, 256 and 512 kept points (index 0..6). A voxel solved in FP64 takes
+ * the wave or block solver up to 16 points and the strip solver (FP64 matrix cores) above.
+ * Defaults come from the project's autotuner on the spinning-scan workload.
  */
 typedef struct {
   int32_t fp32_last_bucket;   /* FP32 mode: buckets 0..this run in float first (-1: none) */
-  int32_t wave_last_bucket;   /* grids of up to 64 points: buckets 0..this use the one-voxel-per-
-                                 wavefront solver (max 2), the others one voxel per workgroup */
+  int32_t wave_last_bucket;   /* buckets 0..this (max 2) use the one-voxel-per-wavefront solver in
+                                 FP32, and bucket 0 in FP64, where the grid's rows fit (256 points
+                                 up to 32, 64 points up to 64), the others one voxel per workgroup */
   int32_t streams;            /* 1: every bucket on the context's stream; 3: buckets fork onto
                                  the three side streams as bucket_stream says and join back */
   int32_t grid_scale[7];      /* persistent grid of bucket b = grid_scale[b] / 4 x the resident
                                  workgroups the device holds (1..64; buckets 5 and 6 use at
                                  most 4, one resident wave of workgroups) */
-  int32_t tile_first_bucket;  /* buckets from this one on (2..5) run a tiled solver on the
-                                 matrix cores (FP64, or the mixed form in MIXED mode); buckets
-                                 5 and 6 always do */
-  int32_t tiled_first;        /* with streams = 3: 1 runs the tiled buckets first, alone on the
-                                 context's stream (their workgroups need whole CUs, which other
-                                 buckets' workgroups would hold), and forks the others after
-                                 them; 0 forks every bucket at once */
+  int32_t tile_first_bucket;  /* buckets from this one on (2..5) never run in float: the mixed
+                                 tiled solver in MIXED mode, else the strip solver in FP64;
+                                 buckets 5 and 6 always do */
+  int32_t tiled_first;        /* with streams = 3: 1 runs the buckets from tile_first_bucket on
+                                 first, alone on the context's stream, and forks the others
+                                 after them; 0 forks every bucket at once */
   int32_t bucket_stream[7];   /* with streams = 3: stream of bucket b, 0 the context's stream,
                                  1..3 the side streams; buckets on one stream run one after
                                  another, largest first (default {0, 2, 2, 1, 1, 3, 3}: 16
                                  points on the context's stream, 96/128, 32/64 and 256/512
                                  points each on one side stream) */
   int32_t tiled_merge;        /* 1: the 256- and 512-point buckets run as one longest-first
-                                 launch of the 512-point tiled solver (the smaller voxels fill
+                                 launch of the 512-point solver (the smaller voxels fill
                                  the CUs the larger ones leave idle); 0: one launch each */
 } vgpr_tuning;
 
@@ -457,8 +457,8 @@ VGPR_API vgpr_status vgpr_get_tuning(const vgpr_ctx* ctx, vgpr_tuning* t);
  * launches since the last read of that family, then resets it. Families:
  * "voxelize_key", "voxelize_sort" (all radix passes of a call),
  * "voxelize_segment", "classify" (tau test, frames and bucket slots), "nan_rows"
- * (the rows of voxels below tau), "gauss_init", "structure_loss" (the ring-search
- * kernel of vgpr_structure_loss), "structure_loss_brute" (its brute-force pass
+ * (the rows of voxels below tau; fewer than 32,768 voxels: part of "classify"), "gauss_init", "structure_loss" (the ring-search
+ * kernels of vgpr_structure_loss), "structure_loss_brute" (its brute-force pass
  * over points far from every Gaussian), "fit_mix_n<C>" (MIXED mode tiled
  * solver), "fit_f32_n<C>" / "fit_f64_n<C>" (the
  * per-voxel solver over the size bucket of capacity C = 16, 32, 64, 96, 128, 256, 512) and

@@ -1,8 +1,8 @@
 """Launch autotuner of vgpr_fit_predict.
 
 Searches the launch choices of `vgpr_tuning` (which buckets try FP32 first,
-which use the one-voxel-per-wavefront solver, which use the tiled
-matrix-core solver, one or three streams and which stream each bucket takes,
+which use the one-voxel-per-wavefront solver, from which on none runs in
+float (MIXED: the tiled solver), one or three streams and which stream each bucket takes,
 the persistent grid size of each bucket) by coordinate descent, timing the real
 workload on the device with HIP events. A candidate is accepted only if its
 outputs stay within the accuracy tolerances of an FP64 reference run of the

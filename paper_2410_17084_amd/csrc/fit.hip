@@ -1,17 +1,15 @@
 // vgpr_fit_predict: Alg. 1 after STORE, Eq. (1)-(3) of the paper, per voxel.
 //
-// Three kernels per call (plus a re-solve pass in FP32 mode):
+// Three steps per call (plus refinement and re-solve passes in FP32 mode):
 //
-// 1. prep (one thread per voxel): kept count n, tau test, a slot in the
-//    voxel's size bucket (one atomic per wavefront and bucket), the PCA frame
+// 1. prep (64 voxels a workgroup): kept count n, tau test, a slot in the
+//    voxel's size bucket (one atomic per workgroup and bucket), the PCA frame
 //    of Alg. 1 in double (centroid, covariance, cyclic Jacobi eigen-solve,
 //    value axis = world axis closest to the smallest-eigenvalue eigenvector,
 //    cyclic parameter axes, near-tie flag, optional per-voxel length scale)
 //    written as a 64-byte slot record, and the kept points staged as float4
 //    (x, y, z, noise variance) at their sorted positions, so that the solvers
-//    read one record and one coalesced row of points per voxel. Voxels of more
-//    than 64 points are staged and summed by a second kernel, one wavefront
-//    per voxel, so that no thread walks up to 512 points alone.
+//    read one record and one coalesced row of points per voxel.
 // 2. solve: the posterior of Eq. (3) from an LDL^T elimination of the
 //    augmented system whose rows are
 //          [ K + S | f~ ]   n data rows      (S = noise variances on the diagonal)
@@ -22,20 +20,26 @@
 //      var_q  = s_f^2 - sum_j a_qj^2 / d_j      (diagonal of Sigma*)
 //      mean_q = mu    + sum_j a_qj * y_j / d_j   (K*^T (K+S)^-1 f~)
 //    accumulate on the fly (d_j = pivots, a_qj = the query row's entry at
-//    step j). K, K* and K** are never stored. Each row lives in registers;
-//    after step j it shifts by one register so the active column is always
-//    element 0 (no dynamic register indexing).
-//    - wave solver (n <= 64, m <= 64): one voxel per wavefront, lane l holds
-//      query row l and data row l; column j is broadcast with readlane, so
-//      the elimination has no barriers at all.
-//    - block solver (larger voxels or grids): one voxel per workgroup, one
+//    step j). K, K* and K** are never stored.
+//    - wave solver (16 points in either precision; FP32 up to 64 points and 64
+//      queries): one voxel per wavefront, lane l holds query row l and data
+//      row l; column j is broadcast with readlane, so the elimination has no
+//      barriers at all. For 16 points the steps are unrolled in place, above
+//      that each row shifts by one register a step so that the active column
+//      is always element 0 (no dynamic register indexing).
+//    - strip solver (FP64 above 16 points, fit_strip.h): Cholesky in strips of
+//      16 on the FP64 matrix cores, one wavefront a voxel up to 64 points.
+//    - block solver (FP32 buckets above 16 points, and the 16-point bucket
+//      where the wave solver is switched off): one voxel per workgroup, one
 //      row per lane, column j broadcast through LDS with one barrier a step.
-// 3. NaN rows for voxels below tau.
+//    - mixed tiled solver (MIXED mode's larger buckets): FP32 tiles on the FP32
+//      matrix cores.
+// 3. NaN rows for voxels below tau (few voxels: written by prep).
 //
-// The elimination type T is float or double. In FP32 mode every voxel runs
-// in float and voxels whose refinement score sum_j |y_j| / d_j exceeds the
-// threshold (the amplification of FP32 rounding in K^-1 f~) are re-solved in
-// double; in FP64 mode every voxel runs in double.
+// The elimination type T is float or double. In FP32 mode the buckets up to
+// fp32_last_bucket run in float, and voxels whose refinement score sum_j |y_j| / d_j
+// exceeds the threshold (the amplification of FP32 rounding in K^-1 f~) are refined
+// or re-solved in double; in FP64 mode every voxel runs in double.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
