@@ -38,12 +38,12 @@ TRAFFIC_FILES = {"aggregated": os.path.join(HERE, "profiles", "hbm_traffic_aggre
 
 def source_hash() -> str:
     """Hash of the sources the solver kernels and their launches are built from (the
-    solver file, the context and launch-choice code, the internal and ABI headers):
+    solver files, the context and launch-choice code, the internal and ABI headers):
     ties stored counter readings of the solver kernels to the code."""
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(HERE, "paper_2410_17084_amd", "csrc")
-    files = [os.path.join(csrc, f) for f in ("ctx.hip", "fit.hip", "scan.h", "vgpr_internal.h")] + \
+    files = [os.path.join(csrc, f) for f in ("ctx.hip", "fit.hip", "fit_strip.h", "scan.h", "vgpr_internal.h")] + \
         [os.path.join(HERE, "include", "vgpr.h")]
     for f in files:
         h.update(os.path.basename(f).encode())

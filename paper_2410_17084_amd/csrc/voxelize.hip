@@ -322,8 +322,7 @@ __global__ void __launch_bounds__(kComposeThreads) compose_kernel(
       const size_t i = base + r * kComposeThreads + threadIdx.x;
       k[r] = i < n ? keys[i] : kKeySentinel;
     }
-    if (frames)
-      while (f < nf - 1 && fo[f + 1] <= (int64_t)base) ++f;
+    if (frames && fo[f + 1] <= (int64_t)base) f = frame_of((uint32_t)(base < n ? base : n - 1), fo, nf);
     const int64_t frame_end = frames ? fo[f + 1] : 0;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -582,7 +581,8 @@ constexpr unsigned long long kSegAlone = 1ull << 62, kSegUpTo = 1ull << 63, kSeg
 // the number of heads before element fo[f].
 template <typename K, int NT>
 __global__ void __launch_bounds__(NT) segment_kernel(
-    const K* __restrict__ keys_a, const K* __restrict__ keys_b, uint32_t n, const KeyForm* __restrict__ form, const int64_t* __restrict__ fo, int nf, unsigned long long* __restrict__ status,
+    const K* __restrict__ keys_a, const K* __restrict__ keys_b, uint32_t n, const KeyForm* __restrict__ form,
+    const int64_t* __restrict__ fo, int nf, unsigned long long* __restrict__ status,
     uint32_t ntiles, uint32_t* __restrict__ ticket, int64_t cap, uint64_t* __restrict__ out_keys,
     int32_t* __restrict__ out_off, int32_t* __restrict__ out_cnt, unsigned long long* __restrict__ h_res) {
   constexpr int kTile = NT * kSegItems;
@@ -732,7 +732,8 @@ vgpr_status voxelize_impl(vgpr_ctx* ctx, const float* d_xyz, int64_t n_pts, cons
   const uint32_t min_tile =
       small ? kSmallThreads * kSmallItems : std::min(kLargeThreads * kLargeItems, kWideThreads * kWideItems);
   const uint32_t max_tiles = (uint32_t)((n_pts + min_tile - 1) / min_tile);
-  const uint32_t nseg = (uint32_t)((n_pts + kSegItems * (small ? kSmallSeg : kLargeSeg) - 1) / (kSegItems * (small ? kSmallSeg : kLargeSeg)));
+  const int seg_tile = kSegItems * (small ? kSmallSeg : kLargeSeg);
+  const uint32_t nseg = (uint32_t)((n_pts + seg_tile - 1) / seg_tile);
   const uint32_t kblocks = (uint32_t)std::min<int64_t>((n_pts + kKeyThreads * kKeyItems - 1) / (kKeyThreads * kKeyItems),
                                                        kKeyBlocks);
   // words cleared by the key kernel: segmentation look-back, histograms, tickets, the first pass's look-back
