@@ -256,7 +256,10 @@ VGPR_API vgpr_status vgpr_fit_predict_noalloc(vgpr_ctx* ctx, const float* d_xyz,
  * stored points back to back (28 bytes per point with the solver's copy),
  * about 510 bytes per re-solved voxel, and the larger solvers' fixed scratch
  * when max_pts > 128 (MIXED mode: above 64). An update's scratch therefore scales with the voxels it
- * re-solves, not with max_voxels.
+ * re-solves, not with max_voxels. A context without an HBM budget keeps the
+ * memory of one destroyed map (up to 512 MiB, not in vgpr_workspace_bytes) for
+ * its next map, until it is destroyed, a larger one takes its place or one of
+ * its allocations would fail.
  */
 VGPR_API vgpr_status vgpr_map_create(vgpr_ctx* ctx, const vgpr_params* params, int64_t max_voxels,
                             vgpr_map** out);

@@ -64,6 +64,7 @@ vgpr_status reserve_buffer(vgpr_ctx* ctx, DeviceBuffer& buf, size_t bytes, const
   buf = DeviceBuffer{};
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, want);
+  if (e != hipSuccess && drop_spare(ctx)) e = hipMalloc(&p, want);
   if (e != hipSuccess) return hip_fail(ctx, e, &buf == &ctx->stage ? "hipMalloc(map staging)" : "hipMalloc(workspace)");
   buf.ptr = p;
   buf.bytes = want;
@@ -94,6 +95,7 @@ vgpr_status alloc_owned(vgpr_ctx* ctx, void** p, size_t bytes) {
   if (ctx->budget && ctx->held + bytes > ctx->budget)
     return fail(ctx, VGPR_E_BUDGET, "allocation of " + std::to_string(bytes) + " bytes exceeds the HBM budget");
   hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && drop_spare(ctx)) e = hipMalloc(p, bytes);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
   ctx->held += bytes;
   return VGPR_OK;
@@ -102,6 +104,38 @@ vgpr_status alloc_owned(vgpr_ctx* ctx, void** p, size_t bytes) {
 void free_owned(vgpr_ctx* ctx, void* p, size_t bytes) {
   if (!p) return;
   (void)hipFree(p);
+  ctx->held -= bytes;
+}
+
+bool drop_spare(vgpr_ctx* ctx) {
+  if (!ctx->spare.ptr) return false;
+  (void)hipGetLastError();  // of the allocation that failed, if one did
+  (void)hipFree(ctx->spare.ptr);
+  ctx->spare = DeviceBuffer{};
+  return true;
+}
+
+vgpr_status take_map_block(vgpr_ctx* ctx, void** p, size_t* bytes) {
+  // not a block that is mostly unused
+  if (ctx->spare.ptr && !ctx->budget && ctx->spare.bytes >= *bytes && ctx->spare.bytes / 2 <= *bytes) {
+    VGPR_HIP(ctx, hipMemsetAsync(ctx->spare.ptr, 0, ctx->spare.bytes, ctx->stream));
+    *p = ctx->spare.ptr;
+    *bytes = ctx->spare.bytes;
+    ctx->held += ctx->spare.bytes;
+    ctx->spare = DeviceBuffer{};
+    return VGPR_OK;
+  }
+  return alloc_owned(ctx, p, *bytes);
+}
+
+void give_map_block(vgpr_ctx* ctx, void* p, size_t bytes) {
+  if (ctx->budget || bytes > kSpareBytes || bytes <= ctx->spare.bytes) {
+    free_owned(ctx, p, bytes);
+    return;
+  }
+  drop_spare(ctx);
+  ctx->spare.ptr = p;
+  ctx->spare.bytes = bytes;
   ctx->held -= bytes;
 }
 
@@ -252,6 +286,7 @@ vgpr_status vgpr_destroy(vgpr_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   if (ctx->work.ptr) (void)hipFree(ctx->work.ptr);
   if (ctx->stage.ptr) (void)hipFree(ctx->stage.ptr);
+  drop_spare(ctx);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   for (auto& kv : ctx->prof)
     for (auto& pr : kv.second.pending) {

@@ -475,9 +475,9 @@ vgpr_status vgpr_map_create_ex(vgpr_ctx* ctx, const vgpr_params* params, int64_t
   const size_t o_pool = sub(sizeof(float) * 3 * cap * max_voxels), o_ctr = sub(sizeof(unsigned long long) * 8);
   const size_t o_pred = update_mode == 1 ? sub(sizeof(float4) * (size_t)m * max_voxels) : 0;
   const size_t o_vp = update_mode == 1 ? sub(max_voxels) : 0;
-  const size_t total = (off + 255) & ~size_t(255);
+  size_t total = (off + 255) & ~size_t(255);
   void* blk = nullptr;
-  st = alloc_owned(ctx, &blk, total);
+  st = take_map_block(ctx, &blk, &total);
   if (st != VGPR_OK) {
     delete M;
     return st;
@@ -519,7 +519,7 @@ vgpr_status vgpr_map_destroy(vgpr_map* M) {
   vgpr_ctx* ctx = M->ctx;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
-  free_owned(ctx, M->block, M->bytes);
+  give_map_block(ctx, M->block, M->bytes);
   ctx->live_maps -= 1;
   delete M;
   return VGPR_OK;

@@ -121,3 +121,32 @@ def test_loss_ring_edges(env, n):  # noqa: F811
         assert (np.abs(got[cell][0] - ref) <= tol).all()
         assert abs(loss - ref.mean()) <= tol.max()
     assert np.array_equal(got[h][0], got[0.5][0]) and np.array_equal(got[h][1], got[0.5][1])
+
+
+def test_map_block_taken_again(env):  # noqa: F811
+    """A map in a block that another map left behaves, and is exported, as one in a new block."""
+    torch, vgpr, ctx = env
+    w = dict(configs.params_for("paper_stream"), max_pts=20, min_pts=4)
+    p = parity.gpu_params(vgpr, w)
+    r = np.random.default_rng(3)
+    a, b = (dev(torch, r.uniform(-3, 3, (n, 3)) * [1, 1, 0.1]) for n in (6000, 4000))
+
+    def session(c, x, size, feedback):
+        m = vgpr.Map(c, p, max_voxels=size, feedback=feedback)
+        got = [t.cpu().numpy().copy() for t in m.update(x)] + [np.frombuffer(m.export(), np.uint8)]
+        m.close()
+        return got
+
+    for feedback in (False, True):
+        say("map block", feedback)
+        own = vgpr.Context(0)
+        held = own.workspace_bytes()
+        session(own, a, 9000, feedback)
+        again = session(own, b, 8000, feedback)  # in the first map's block
+        assert own.workspace_bytes() - held < (1 << 30)
+        fresh = vgpr.Context(0)
+        for e, g in zip(session(fresh, b, 8000, feedback)[:4], again[:4]):
+            assert np.array_equal(np.sort(e.ravel()), np.sort(g.ravel()), equal_nan=e.dtype.kind == "f")
+        assert len(session(fresh, b, 8000, feedback)[4]) == len(again[4])
+        own.close()
+        fresh.close()
