@@ -38,7 +38,7 @@ constexpr size_t strip_scratch_doubles(int ns) { return strip_lds(ns) ? 0 : (siz
 
 // 2^t for t <= 0: t split into an integer and |f| <= 1/2 (exactly), 2^f by its Chebyshev
 // interpolant of degree 11 (within 4e-18), scaled by the exponent. Far below the smallest
-// exponent the result is 0, which is what the padded points rely on.
+// exponent the result is 0, which is what the padded points rely on. (So it is for a NaN, which the caller keeps out.)
 __device__ __forceinline__ double exp2_neg(double t) {
   t = fmax(t, -2000.0);  // (also keeps a product in the argument from being contracted into the subtraction)
   const double n = __builtin_rint(t);
@@ -358,6 +358,11 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
   };
 
   if (tid < P.nq) s_frac[tid] = grid_frac(P, tid);
+  if (tid == 0) {  // for the first voxel; the end of each clears them for the next
+    s_fail = 0;
+    s_maxvar = 0u;
+  }
+  sync();
   int item = (int)blockIdx.x;
   while (item < items) {
     const int slot = slots ? slots[item] : item;
@@ -366,10 +371,6 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
     const RotRec* rot = rots ? rots + slot : nullptr;
     const int n = fr.n;
     const int nb = (n + kStrip - 1) / kStrip;
-    if (tid == 0) {
-      s_fail = 0;
-      s_maxvar = 0u;
-    }
     // coordinates scaled so that kappa = s_f^2 2^-(du^2 + dw^2); the padding points lie so far from the
     // data, the queries and each other that their kernel entries are zero
     const double lam2 = fr.lam * 1.4426950408889634;
@@ -389,6 +390,9 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
         xu *= sc;
         xw *= sc;
         nz = pt.w;
+        // a point that is not finite fails its voxel here: exp2_neg would make 0 of a NaN distance, and an
+        // infinite pivot in the last place is positive and followed by none
+        if (!(isfinite(xu) && isfinite(xw) && isfinite(fv) && isfinite(nz))) s_fail = 1;
       }
       pu[i] = xu;
       pw[i] = xw;
@@ -628,8 +632,11 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
     if (lane == 0) atomicMax(&s_maxvar, __float_as_uint(maxvar));
     if (tid == 0) s_item = (int)ahead;
     sync();
-    if (tid == 0)
+    if (tid == 0) {
       finish_voxel(P, io, rec.v, slot, rec.cnt, fr.axes, s_fail != 0, false, __uint_as_float(s_maxvar), nullptr, nullptr);
+      s_fail = 0;
+      s_maxvar = 0u;
+    }
     item = __builtin_amdgcn_readfirstlane(s_item);
     sync();
   }
