@@ -46,6 +46,9 @@ struct vgpr_map {
   float4* pred = nullptr;    // mode 1: m predicted rows (x, y, z, var) per voxel
   uint8_t* vpred = nullptr;  // mode 1: the voxel holds a prediction (it is in the map)
   int64_t host_voxels = 0;   // voxels held, as read back after the last update (host copy)
+  hipStream_t stream = nullptr;  // of the last update: its solve may still be running there
+  bool updated = false;
+  bool one_stream = true;  // all updates' work is ordered on `stream`
 };
 
 namespace vgpr {
@@ -518,8 +521,13 @@ vgpr_status vgpr_map_destroy(vgpr_map* M) {
   if (!M) return VGPR_E_INVALID;
   vgpr_ctx* ctx = M->ctx;
   (void)hipSetDevice(ctx->device);
-  (void)hipStreamSynchronize(ctx->stream);
-  give_map_block(ctx, M->block, M->bytes);
+  // The last update's solve may still write the block. The block is handed on only if all updates ran on the
+  // stream that is waited for here; else it is freed, which waits for the device.
+  const bool waited = hipStreamSynchronize(ctx->stream) == hipSuccess;
+  if (waited && (!M->updated || (M->one_stream && M->stream == ctx->stream)))
+    give_map_block(ctx, M->block, M->bytes);
+  else
+    free_owned(ctx, M->block, M->bytes);
   ctx->live_maps -= 1;
   delete M;
   return VGPR_OK;
@@ -537,6 +545,9 @@ vgpr_status vgpr_map_update(vgpr_map* M, const float* d_xyz, int64_t n_pts, uint
     return fail(ctx, VGPR_E_INVALID, "output buffer is NULL");
   if (n_pts == 0) return VGPR_OK;
   if (hipSetDevice(ctx->device) != hipSuccess) return fail(ctx, VGPR_E_DEVICE, "hipSetDevice");
+  M->one_stream = M->one_stream && (!M->updated || M->stream == ctx->stream);
+  M->updated = true;
+  M->stream = ctx->stream;
   const vgpr_params& p = M->params;
   const int64_t n = n_pts;
   const int64_t nblk = (n + kCompactTile - 1) / kCompactTile;
@@ -644,6 +655,7 @@ vgpr_status vgpr_map_update(vgpr_map* M, const float* d_xyz, int64_t n_pts, uint
     VGPR_HIP(ctx, hipGetLastError());
     FitArgs a{sxyz, npts, ukey, soff, scnt, nullptr, snz, nout, d_out, d_axis, d_status};
     st = fit_predict_impl(ctx, a, &pf, 0, sb + s_fit);
+    if (st != VGPR_OK) M->one_stream = false;  // side streams may not have joined
     if (st != VGPR_OK) return st;
     hipLaunchKernelGGL(feedback_state_kernel, dim3((unsigned)((nout * m + 255) / 256)), dim3(256), 0, ctx->stream,
                        *M, uid, scap, reinterpret_cast<const float4*>(d_out), d_status, nout, m);
@@ -671,6 +683,7 @@ vgpr_status vgpr_map_update(vgpr_map* M, const float* d_xyz, int64_t n_pts, uint
     VGPR_HIP(ctx, hipGetLastError());
     FitArgs a{sxyz, npts, ukey, soff, ucnt, nullptr, nullptr, nout, d_out, d_axis, d_status};
     st = fit_predict_impl(ctx, a, &p, 0, sb + s_fit);
+    if (st != VGPR_OK) M->one_stream = false;  // side streams may not have joined
     if (st != VGPR_OK) return st;
     hipLaunchKernelGGL(state_kernel, dim3((unsigned)((nout + 255) / 256)), dim3(256), 0, ctx->stream, *M, uid,
                        d_status, nout);
