@@ -151,7 +151,8 @@ VGPR_API vgpr_status vgpr_set_stream(vgpr_ctx* ctx, void* hip_stream);
  * with ctx = NULL, why the calling thread's last vgpr_create failed. */
 VGPR_API const char* vgpr_last_error(const vgpr_ctx* ctx);
 /* Device bytes the context currently holds: its scratch, the staging area of
- * its maps' updates, and the maps created on it. */
+ * its maps' updates, the maps created on it, and the memory of a destroyed map
+ * that it keeps for its next one (vgpr_map_create). */
 VGPR_API size_t vgpr_workspace_bytes(const vgpr_ctx* ctx);
 
 /*
@@ -257,9 +258,11 @@ VGPR_API vgpr_status vgpr_fit_predict_noalloc(vgpr_ctx* ctx, const float* d_xyz,
  * about 510 bytes per re-solved voxel, and the larger solvers' fixed scratch
  * when max_pts > 128 (MIXED mode: above 64). An update's scratch therefore scales with the voxels it
  * re-solves, not with max_voxels. A context without an HBM budget keeps the
- * memory of one destroyed map (up to 512 MiB, not in vgpr_workspace_bytes) for
- * its next map, until it is destroyed, a larger one takes its place or one of
- * its allocations would fail.
+ * memory of its last destroyed map for its next map: up to 512 MiB over all
+ * contexts of the process, and only while an eighth of the GPU's memory is
+ * unused. It is given back when the context is destroyed, when the next map
+ * cannot use it (it does not fit, or would leave more than half of it unused)
+ * and when an allocation of any context on that GPU would fail.
  */
 VGPR_API vgpr_status vgpr_map_create(vgpr_ctx* ctx, const vgpr_params* params, int64_t max_voxels,
                             vgpr_map** out);

@@ -64,7 +64,7 @@ vgpr_status reserve_buffer(vgpr_ctx* ctx, DeviceBuffer& buf, size_t bytes, const
   buf = DeviceBuffer{};
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, want);
-  if (e != hipSuccess && drop_spare(ctx)) e = hipMalloc(&p, want);
+  if (e != hipSuccess && drop_spares(ctx->device)) e = hipMalloc(&p, want);
   if (e != hipSuccess) return hip_fail(ctx, e, &buf == &ctx->stage ? "hipMalloc(map staging)" : "hipMalloc(workspace)");
   buf.ptr = p;
   buf.bytes = want;
@@ -95,7 +95,7 @@ vgpr_status alloc_owned(vgpr_ctx* ctx, void** p, size_t bytes) {
   if (ctx->budget && ctx->held + bytes > ctx->budget)
     return fail(ctx, VGPR_E_BUDGET, "allocation of " + std::to_string(bytes) + " bytes exceeds the HBM budget");
   hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && drop_spare(ctx)) e = hipMalloc(p, bytes);
+  if (e != hipSuccess && drop_spares(ctx->device)) e = hipMalloc(p, bytes);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
   ctx->held += bytes;
   return VGPR_OK;
@@ -107,36 +107,87 @@ void free_owned(vgpr_ctx* ctx, void* p, size_t bytes) {
   ctx->held -= bytes;
 }
 
-bool drop_spare(vgpr_ctx* ctx) {
-  if (!ctx->spare.ptr) return false;
-  (void)hipGetLastError();  // of the allocation that failed, if one did
-  (void)hipFree(ctx->spare.ptr);
-  ctx->spare = DeviceBuffer{};
-  return true;
+namespace {
+struct Spare {
+  const vgpr_ctx* owner;
+  int device;
+  void* ptr;
+  size_t bytes;
+};
+std::mutex g_spare_mu;
+std::vector<Spare> g_spares;  // at most one a context
+
+// Frees the blocks that `which` picks (with the lock held).
+template <typename F>
+bool free_spares(F&& which) {
+  bool any = false;
+  for (size_t i = g_spares.size(); i-- > 0;) {
+    if (!which(g_spares[i])) continue;
+    (void)hipFree(g_spares[i].ptr);
+    g_spares.erase(g_spares.begin() + (ptrdiff_t)i);
+    any = true;
+  }
+  return any;
+}
+}  // namespace
+
+bool drop_spares(int device) {
+  std::lock_guard<std::mutex> lk(g_spare_mu);
+  const bool any = free_spares([&](const Spare& s) { return s.device == device; });
+  if (any) (void)hipGetLastError();  // of the allocation that failed
+  return any;
+}
+
+void drop_spare(const vgpr_ctx* ctx) {
+  std::lock_guard<std::mutex> lk(g_spare_mu);
+  free_spares([&](const Spare& s) { return s.owner == ctx; });
+}
+
+size_t spare_bytes(const vgpr_ctx* ctx) {
+  std::lock_guard<std::mutex> lk(g_spare_mu);
+  for (const Spare& s : g_spares)
+    if (s.owner == ctx) return s.bytes;
+  return 0;
 }
 
 vgpr_status take_map_block(vgpr_ctx* ctx, void** p, size_t* bytes) {
-  // not a block that is mostly unused
-  if (ctx->spare.ptr && !ctx->budget && ctx->spare.bytes >= *bytes && ctx->spare.bytes / 2 <= *bytes) {
-    VGPR_HIP(ctx, hipMemsetAsync(ctx->spare.ptr, 0, ctx->spare.bytes, ctx->stream));
-    *p = ctx->spare.ptr;
-    *bytes = ctx->spare.bytes;
-    ctx->held += ctx->spare.bytes;
-    ctx->spare = DeviceBuffer{};
-    return VGPR_OK;
+  Spare got{};
+  {
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    for (size_t i = 0; i < g_spares.size(); ++i) {
+      const Spare s = g_spares[i];
+      if (s.owner != ctx || s.bytes < *bytes || s.bytes / 2 > *bytes) continue;
+      g_spares.erase(g_spares.begin() + (ptrdiff_t)i);
+      got = s;
+      break;
+    }
+    if (!got.ptr) free_spares([&](const Spare& s) { return s.owner == ctx; });  // too small, or mostly unused
   }
-  return alloc_owned(ctx, p, *bytes);
+  if (!got.ptr) return alloc_owned(ctx, p, *bytes);
+  ctx->held += got.bytes;
+  if (const hipError_t e = hipMemsetAsync(got.ptr, 0, got.bytes, ctx->stream); e != hipSuccess) {
+    free_owned(ctx, got.ptr, got.bytes);
+    return hip_fail(ctx, e, "hipMemsetAsync(map)");
+  }
+  *p = got.ptr;
+  *bytes = got.bytes;
+  return VGPR_OK;
 }
 
 void give_map_block(vgpr_ctx* ctx, void* p, size_t bytes) {
-  if (ctx->budget || bytes > kSpareBytes || bytes <= ctx->spare.bytes) {
-    free_owned(ctx, p, bytes);
-    return;
+  size_t unused = 0, card = 0;
+  if (!ctx->budget && bytes <= kSpareBytes && hipMemGetInfo(&unused, &card) == hipSuccess && unused >= card / 8) {
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    free_spares([&](const Spare& s) { return s.owner == ctx; });
+    size_t all = bytes;
+    for (const Spare& s : g_spares) all += s.bytes;
+    if (all <= kSpareBytes) {
+      g_spares.push_back({ctx, ctx->device, p, bytes});
+      ctx->held -= bytes;
+      return;
+    }
   }
-  drop_spare(ctx);
-  ctx->spare.ptr = p;
-  ctx->spare.bytes = bytes;
-  ctx->held -= bytes;
+  free_owned(ctx, p, bytes);
 }
 
 static hipEvent_t take_event(vgpr_ctx* ctx) {
@@ -314,7 +365,7 @@ vgpr_status vgpr_set_stream(vgpr_ctx* ctx, void* hip_stream) {
 
 const char* vgpr_last_error(const vgpr_ctx* ctx) { return ctx ? ctx->last_error.c_str() : create_error.c_str(); }
 
-size_t vgpr_workspace_bytes(const vgpr_ctx* ctx) { return ctx ? ctx->held : 0; }
+size_t vgpr_workspace_bytes(const vgpr_ctx* ctx) { return ctx ? ctx->held + spare_bytes(ctx) : 0; }
 
 vgpr_status vgpr_set_tuning(vgpr_ctx* ctx, const vgpr_tuning* t) {
   if (!ctx || !t) return VGPR_E_INVALID;

@@ -64,7 +64,6 @@ struct vgpr_ctx {
   size_t pinned_bytes = 0;
   std::string last_error;
   int cu_count = 0;
-  vgpr::DeviceBuffer spare;   // a destroyed map's block, kept for the next one (not in `held`)
   int live_maps = 0;          // maps created on this context and not yet destroyed
   int live_graphs = 0;        // captured graphs created on this context and not yet destroyed
   vgpr_tuning tune{0, 2, 3, {4, 4, 4, 4, 4, 4, 4}, 5, 0, {0, 2, 2, 1, 1, 3, 3}, 0};
@@ -100,15 +99,19 @@ vgpr_status reserve_pinned(vgpr_ctx* ctx, size_t bytes);
 vgpr_status alloc_owned(vgpr_ctx* ctx, void** p, size_t bytes);
 void free_owned(vgpr_ctx* ctx, void* p, size_t bytes);
 
-// Blocks of maps. A context without an HBM budget keeps one destroyed map's block of up to
-// kSpareBytes for its next map: the driver clears memory before it hands it out again, so a
-// session a map waits 0.35 ms for hipMalloc and hipFree, and 3 ms once sessions have gone
-// through the card's memory. Given back when the context is destroyed, when a larger one takes
-// its place, and when an allocation of the context fails. A block taken again is zeroed.
+// Blocks of maps. A context without an HBM budget keeps the block of its last destroyed map for
+// its next map: the driver clears memory before it hands it out again, so a session a map waits
+// 0.35 ms for hipMalloc and hipFree, and 3 ms once sessions have gone through the card's memory.
+// The process keeps at most kSpareBytes of them, and only while an eighth of the card is unused.
+// A block is given back when the context is destroyed, when its next map does not fit it or would
+// leave more than half of it unused, and when an allocation of any context on its GPU fails. It is
+// zeroed when it is taken again.
 constexpr size_t kSpareBytes = size_t(512) << 20;
 vgpr_status take_map_block(vgpr_ctx* ctx, void** p, size_t* bytes);
 void give_map_block(vgpr_ctx* ctx, void* p, size_t bytes);
-bool drop_spare(vgpr_ctx* ctx);
+size_t spare_bytes(const vgpr_ctx* ctx);
+void drop_spare(const vgpr_ctx* ctx);
+bool drop_spares(int device);  // of every context
 
 // Carve aligned sub-buffers out of the workspace.
 struct Carver {

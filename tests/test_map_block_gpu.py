@@ -81,3 +81,59 @@ def test_map_closed_on_another_stream(env, feedback):  # noqa: F811
             del kept
             torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("feedback", [False, True])
+def test_map_in_a_kept_block(env, feedback):  # noqa: F811
+    """Two sessions of several updates in one context, the second in the first's (larger) block: what
+    the second returns and exports equals a new context's, voxel by voxel."""
+    torch, vgpr, _ = env
+    p = _params(vgpr)
+    say("map in a kept block", feedback)
+    first, second = _frames(torch, 7, 9000, 4), _frames(torch, 8, 5000, 4)
+    fresh = vgpr.Context(0)
+    expect = _session(vgpr, fresh, p, second, 6000, feedback)
+    fresh.close()
+    ctx = vgpr.Context(0)
+    _session(vgpr, ctx, p, first, 9000, feedback)
+    held = ctx.workspace_bytes()
+    m = vgpr.Map(ctx, p, max_voxels=6000, feedback=feedback)
+    assert ctx.workspace_bytes() == held  # the map is in the kept block
+    m.close()
+    assert _same(expect, _session(vgpr, ctx, p, second, 6000, feedback))
+    assert ctx.workspace_bytes() == held
+    ctx.close()
+
+
+def test_kept_blocks_are_counted_and_bounded(env):  # noqa: F811
+    torch, vgpr, _ = env
+    p = _params(vgpr)
+    say("kept blocks")
+    ctxs = [vgpr.Context(0) for _ in range(4)]
+    none = [c.workspace_bytes() for c in ctxs]
+    free = torch.cuda.mem_get_info()[0]
+    for c in ctxs:  # about 200 MB each
+        vgpr.Map(c, p, max_voxels=600000).close()
+    kept = [c.workspace_bytes() - b for c, b in zip(ctxs, none)]
+    assert kept[0] > (128 << 20) and sum(kept) <= (512 << 20)
+    assert free - torch.cuda.mem_get_info()[0] <= sum(kept) + (64 << 20)
+    # a map that would leave most of the block unused does not keep it from the others
+    vgpr.Map(ctxs[0], p, max_voxels=1000).close()
+    assert ctxs[0].workspace_bytes() - none[0] < (8 << 20)
+    # one that does not fit takes its place
+    vgpr.Map(ctxs[0], p, max_voxels=20000).close()
+    small = ctxs[0].workspace_bytes()
+    m = vgpr.Map(ctxs[0], p, max_voxels=20000)
+    assert ctxs[0].workspace_bytes() == small
+    m.close()
+    # over the bound, and with an HBM budget, nothing is kept
+    m = vgpr.Map(ctxs[3], p, max_voxels=2000000)
+    assert ctxs[3].workspace_bytes() - none[3] > (512 << 20)
+    m.close()
+    assert ctxs[3].workspace_bytes() == none[3]
+    own = vgpr.Context(0, hbm_budget=1 << 30)
+    vgpr.Map(own, p, max_voxels=1000).close()
+    assert own.workspace_bytes() == 0
+    own.close()
+    for c in ctxs:
+        c.close()
