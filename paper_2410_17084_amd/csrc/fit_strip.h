@@ -326,6 +326,10 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
   constexpr int D = NS >= 32 ? 4 : (NS == 2 ? 1 : 2);  // tiles in flight
   constexpr int kBatch = NS <= 8 ? 4 : 1;                          // rounds of queries written together
   constexpr int H = NS >= 32 ? 4 : 0;                              // ... of the next column
+  // Voxels of up to 32 points are taken at a fixed stride: they are solved faster than the one counter gives
+  // out numbers (~9 ns each; 20,000 voxels on an 8 x 8 grid 308 us, so 230). Larger ones are not, and differ
+  // more (20,000 of 64 points: counter 595 us, stride 860).
+  constexpr bool kStride = NS == 2;
   constexpr int TS = N + 4;                 // row stride of the query tables (16 rows 4 apart: no bank conflict)
   constexpr int kPub = kTab ? 4 * kTileDbl : 2;
   constexpr int kBig = kLds ? strip_tiles(NS) * kTileDbl : (2 * kMaxGridSide * TS > kPub ? 2 * kMaxGridSide * TS : kPub);
@@ -424,7 +428,7 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
       if (job == njobs) {
         // the next voxel's number is fetched while the queries run: by now the workgroups are apart (all of
         // them asking as they start waited up to 40 us on the one counter)
-        if (tid == 0) ahead = items > (int)gridDim.x ? gridDim.x + atomicAdd(fetch, 1u) : (uint32_t)items;
+        if (!kStride && tid == 0) ahead = items > (int)gridDim.x ? gridDim.x + atomicAdd(fetch, 1u) : (uint32_t)items;
         sync();  // the factor is complete
         if constexpr (kTab) {
           // kappa factors over the grid's rows and columns: two tables of n_q x n entries
@@ -630,14 +634,14 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) maxvar = fmaxf(maxvar, __shfl_xor(maxvar, d, 64));
     if (lane == 0) atomicMax(&s_maxvar, __float_as_uint(maxvar));
-    if (tid == 0) s_item = (int)ahead;
+    if (!kStride && tid == 0) s_item = (int)ahead;
     sync();
     if (tid == 0) {
       finish_voxel(P, io, rec.v, slot, rec.cnt, fr.axes, s_fail != 0, false, __uint_as_float(s_maxvar), nullptr, nullptr);
       s_fail = 0;
       s_maxvar = 0u;
     }
-    item = __builtin_amdgcn_readfirstlane(s_item);
+    item = kStride ? item + (int)gridDim.x : __builtin_amdgcn_readfirstlane(s_item);
     sync();
   }
 }

@@ -150,3 +150,29 @@ def test_map_block_taken_again(env):  # noqa: F811
         assert len(session(fresh, b, 8000, feedback)[4]) == len(again[4])
         own.close()
         fresh.close()
+
+
+@pytest.mark.parametrize("n_vox", [1, 767, 768, 769, 3071, 3072, 3073, 6145, 9300])
+def test_strip_voxels_at_a_stride(env, n_vox):  # noqa: F811
+    """FP64 voxels of 17 to 32 points, fewer and more than the launch's wavefronts: every voxel is
+    solved, as in calls on parts of them (bit for bit)."""
+    torch, vgpr, ctx = env
+    r = np.random.default_rng(n_vox)
+    counts = r.integers(17, 33, n_vox)
+    side = int(np.ceil(np.sqrt(n_vox)))
+    cell = np.stack([np.arange(n_vox) // side, np.arange(n_vox) % side, np.zeros(n_vox)], 1)
+    xyz = (np.repeat(cell, counts, 0) + r.uniform(0.05, 0.95, (counts.sum(), 3)) * [1, 1, 0.2]) * 0.5
+    w = dict(configs.params_for("spin32"), max_pts=32, min_pts=3, grid_side=5)
+    say("strip stride", n_vox)
+    x = dev(torch, xyz)
+    p = parity.gpu_params(vgpr, w, precision=vgpr.PREC_FP64)
+    v = ctx.voxelize(x, p)
+    assert v.n_vox == n_vox
+    whole = [t.cpu().numpy() for t in ctx.fit_predict(x, v, p)]
+    assert (whole[2] & vgpr.ST_SOLVED).all() and np.isfinite(whole[0]).all()
+    for a in range(0, n_vox, 500):
+        b = min(a + 500, n_vox)
+        part = dataclasses.replace(v, keys=v.keys[a:b].contiguous(), offsets=v.offsets[a:b].contiguous(),
+                                   counts=v.counts[a:b].contiguous(), n_vox=b - a)
+        for e, g in zip(whole, [t.cpu().numpy() for t in ctx.fit_predict(x, part, p)]):
+            assert np.array_equal(e[a:b], g)
