@@ -119,7 +119,12 @@ constexpr int kPrepCoop = 64;
 // 4 87 us, 8 68 us), else 4 (64 frames, cap 128: 4 114 us, 8 134 us).
 constexpr int kPrepVox = 64;
 constexpr int64_t kPrepManyFrom = 32768;
-// Buckets are taken longest voxel first from this many voxels on.
+// Buckets above 64 points are taken longest voxel first from this many voxels on; the 512-point
+// bucket, whose solver has one workgroup a CU, as soon as its voxels may be more than those.
+// FP64, 8 x 8 grid, in arrival order / longest first: 1,000 voxels of 257 to 512 points among
+// 6,000 1,620 / 1,440 us, 400 among 1,000 895 / 645, 100 among 2,000 548 / 550. The 256-point
+// bucket, two workgroups a CU: 600 voxels among 1,000 335 / 310, 1,500 among 4,000 530 / 560,
+// 3,000 among 8,000 830 to 950 / 830 to 1,000.
 constexpr int64_t kOrderFrom = 8192;
 
 __device__ __forceinline__ float k_exp(float x) { return __expf(x); }
@@ -2100,9 +2105,9 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   bool merge_top = false;  // set below, once the launched buckets are known
   auto runs_fp32 = [&](int b) { return fp32 && b <= tu.fp32_last_bucket && b < first_tile_bucket(ctx); };
   // buckets taken longest voxel first: above 64 points one voxel is long enough to be left over at the end
-  // (with few voxels nearly all start at once, and the order costs a launch before the fork)
+  // (the order costs a launch before the fork; see kOrderFrom)
   auto ordered = [&](int b) {
-    if (b == kNumBuckets - 1 && merge_top) return true;
+    if (b == kNumBuckets - 1) return merge_top || a.n_vox > scratch_groups(ctx, b, mixed);
     return a.n_vox >= kOrderFrom && (b >= 3 ? !runs_fp32(b) : b >= first_tile_bucket(ctx));
   };
   auto launch_b = [&](int b) -> vgpr_status {

@@ -176,3 +176,34 @@ def test_strip_voxels_at_a_stride(env, n_vox):  # noqa: F811
                                    counts=v.counts[a:b].contiguous(), n_vox=b - a)
         for e, g in zip(whole, [t.cpu().numpy() for t in ctx.fit_predict(x, part, p)]):
             assert np.array_equal(e[a:b], g)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n_vox,merge", [(255, 0), (256, 0), (257, 0), (400, 0), (400, 1)])
+def test_largest_voxels_in_order(env, n_vox, merge, prec):  # noqa: F811
+    """Voxels of 250 to 512 points, fewer and more than the largest solver's workgroups (the launch
+    then takes the longest first): bit for bit as in calls on few of them."""
+    torch, vgpr, ctx = env
+    r = np.random.default_rng(n_vox)
+    counts = r.integers(250, 520, n_vox)
+    cell = np.stack([np.arange(n_vox) // 20, np.arange(n_vox) % 20, np.zeros(n_vox)], 1)
+    xyz = (np.repeat(cell, counts, 0) + r.uniform(0.05, 0.95, (counts.sum(), 3)) * [1, 1, 0.2]) * 0.5
+    w = dict(configs.params_for("spin32"), max_pts=512, min_pts=3, grid_side=6)
+    p = parity.gpu_params(vgpr, w, precision={"fp64": vgpr.PREC_FP64, "mixed": vgpr.PREC_MIXED}[prec])
+    say("largest voxels", n_vox, merge, prec)
+    x = dev(torch, xyz)
+    old, t = ctx.tuning(), ctx.tuning()
+    t.tiled_merge = merge
+    ctx.set_tuning(t)
+    try:
+        v = ctx.voxelize(x, p)
+        whole = [a.cpu().numpy() for a in ctx.fit_predict(x, v, p)]
+        assert v.n_vox == n_vox and (whole[2] & vgpr.ST_SOLVED).all()
+        for a in range(0, n_vox, 97):
+            b = min(a + 97, n_vox)
+            part = dataclasses.replace(v, keys=v.keys[a:b].contiguous(), offsets=v.offsets[a:b].contiguous(),
+                                       counts=v.counts[a:b].contiguous(), n_vox=b - a)
+            for e, g in zip(whole, [c.cpu().numpy() for c in ctx.fit_predict(x, part, p)]):
+                assert np.array_equal(e[a:b], g)
+    finally:
+        ctx.set_tuning(old)
