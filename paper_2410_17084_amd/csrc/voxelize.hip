@@ -728,23 +728,37 @@ vgpr_status voxelize_impl(vgpr_ctx* ctx, const float* d_xyz, int64_t n_pts, cons
   }
   const uint32_t n = (uint32_t)n_pts;
   const size_t res_words = R_FRAMES + (size_t)nf + 1;
-  const bool small = n <= kSmallSort;
-  const uint32_t min_tile =
-      small ? kSmallThreads * kSmallItems : std::min(kLargeThreads * kLargeItems, kWideThreads * kWideItems);
-  const uint32_t max_tiles = (uint32_t)((n_pts + min_tile - 1) / min_tile);
-  const int seg_tile = kSegItems * (small ? kSmallSeg : kLargeSeg);
-  const uint32_t nseg = (uint32_t)((n_pts + seg_tile - 1) / seg_tile);
-  const uint32_t kblocks = (uint32_t)std::min<int64_t>((n_pts + kKeyThreads * kKeyItems - 1) / (kKeyThreads * kKeyItems),
-                                                       kKeyBlocks);
-  // words cleared by the key kernel: segmentation look-back, histograms, tickets, the first pass's look-back
-  const size_t o_hist = 2 * (size_t)nseg, o_ticket = o_hist + 256 * kMaxPasses, o_status = o_ticket + kMaxPasses + 2;
-  const size_t zero_words = o_status + 256 * published_rows(max_tiles);
-  const size_t words = zero_words + 256 * published_rows(max_tiles);
-
-  const size_t need = work_offset + Carver::round(sizeof(uint64_t) * (size_t)n) * 2 +
-                      Carver::round(sizeof(uint32_t) * (size_t)n) + Carver::round(sizeof(uint32_t) * words) +
-                      Carver::round(sizeof(KeyPart) * (size_t)kblocks) + Carver::round(sizeof(int64_t) * ((size_t)nf + 1)) +
-                      Carver::round(sizeof(KeyForm)) + 4096;
+  struct Layout {
+    uint32_t max_tiles, nseg, kblocks;
+    size_t o_hist, o_ticket, o_status, zero_words, words, need;
+  };
+  auto layout = [&](bool small) {
+    Layout l{};
+    const uint32_t min_tile =
+        small ? kSmallThreads * kSmallItems : std::min(kLargeThreads * kLargeItems, kWideThreads * kWideItems);
+    l.max_tiles = (uint32_t)((n_pts + min_tile - 1) / min_tile);
+    const int seg_tile = kSegItems * (small ? kSmallSeg : kLargeSeg);
+    l.nseg = (uint32_t)((n_pts + seg_tile - 1) / seg_tile);
+    l.kblocks = (uint32_t)std::min<int64_t>((n_pts + kKeyThreads * kKeyItems - 1) / (kKeyThreads * kKeyItems), kKeyBlocks);
+    // words cleared by the key kernel: segmentation look-back, histograms, tickets, the first pass's look-back
+    l.o_hist = 2 * (size_t)l.nseg;
+    l.o_ticket = l.o_hist + 256 * kMaxPasses;
+    l.o_status = l.o_ticket + kMaxPasses + 2;
+    l.zero_words = l.o_status + 256 * published_rows(l.max_tiles);
+    l.words = l.zero_words + 256 * published_rows(l.max_tiles);
+    l.need = work_offset + Carver::round(sizeof(uint64_t) * (size_t)n) * 2 + Carver::round(sizeof(uint32_t) * (size_t)n) +
+             Carver::round(sizeof(uint32_t) * l.words) + Carver::round(sizeof(KeyPart) * (size_t)l.kblocks) +
+             Carver::round(sizeof(int64_t) * ((size_t)nf + 1)) + Carver::round(sizeof(KeyForm)) + 4096;
+    return l;
+  };
+  bool small = n <= kSmallSort;
+  Layout lay = layout(small);
+  // small tiles publish more (22.4 bytes a point, large ones 20.6): not where that is over an HBM budget
+  if (small && ctx->budget && lay.need > ctx->work.bytes && ctx->held - ctx->work.bytes + lay.need > ctx->budget)
+    lay = layout(small = false);
+  const uint32_t max_tiles = lay.max_tiles, nseg = lay.nseg, kblocks = lay.kblocks;
+  const size_t o_hist = lay.o_hist, o_ticket = lay.o_ticket, o_status = lay.o_status, zero_words = lay.zero_words,
+               words = lay.words, need = lay.need;
   vgpr_status st = reserve_work(ctx, need);
   if (st != VGPR_OK) return st;
   st = reserve_pinned(ctx, sizeof(int64_t) * ((size_t)nf + 1) + sizeof(unsigned long long) * res_words + 64);
