@@ -26,3 +26,17 @@ def test_voxelize_in_21_bytes_a_point(env, n, frames):  # noqa: F811
         for f in ("keys", "offsets", "counts", "perm"):
             assert torch.equal(getattr(a, f), getattr(b, f)), f
         tight.close()
+
+
+def test_structure_loss_of_few_points(env):  # noqa: F811
+    torch, vgpr, ctx = env
+    r = np.random.default_rng(4)
+    g = np.zeros((1000, 8), np.float32)
+    g[:, :3] = r.uniform(-2, 2, (1000, 3))
+    g[:, 4:7] = 0.01
+    x, g = dev(torch, r.uniform(-2, 2, (1000, 3))), dev(torch, g)
+    say("loss budget")
+    tight = vgpr.Context(0, hbm_budget=1262016)  # about 170 bytes a Gaussian, 12 a point and 1.1 MB
+    a, b = (c.structure_loss(x, g, 0.2) for c in (tight, ctx))
+    assert a[:2] == b[:2] and torch.equal(a[2], b[2]) and torch.equal(a[3], b[3])
+    tight.close()
