@@ -31,13 +31,18 @@ constexpr int kStrip = 16;
 constexpr int kTileDbl = kStrip * kStrip;  // doubles of one tile
 constexpr int strip_tiles(int ns) { return ns * (ns + 1) / 2; }
 
-// Voxels of up to 128 points keep their tiles in LDS; above that the workgroup owns a scratch area.
+// Voxels of up to 128 points keep their tiles in LDS; above that the workgroup owns a scratch area
+// (256 points: 272 KB of tiles, against 160 KB of LDS).
 constexpr bool strip_lds(int ns) { return ns <= 8; }
+// One wavefront a voxel as long as its tiles leave room for several a CU (64 points: 20 KB), four above: 20,000
+// voxels, 8 x 8 / 16 x 16 grid, four wavefronts against one: 64 points 553 / 922 us against 505 / 1,042 (400 voxels
+// 75 / 90 against 85 / 120), 96 points 1,225 / 1,922 against 1,604 / 3,395, 128 points 1,895 / 3,339 against
+// 3,407 / 7,963.
 constexpr int strip_waves(int ns) { return ns <= 4 ? 1 : 4; }
 constexpr size_t strip_scratch_doubles(int ns) { return strip_lds(ns) ? 0 : (size_t)strip_tiles(ns) * kTileDbl; }
 
 // 2^t for t <= 0: t split into an integer and |f| <= 1/2 (exactly), 2^f by its Chebyshev
-// interpolant of degree 11 (within 4e-18), scaled by the exponent. Far below the smallest
+// interpolant of degree 11 (within 2.0e-17 with the coefficients as rounded here), scaled by the exponent. Far below the smallest
 // exponent the result is 0, which is what the padded points rely on. (So it is for a NaN, which the caller keeps out.)
 __device__ __forceinline__ double exp2_neg(double t) {
   t = fmax(t, -2000.0);  // (also keeps a product in the argument from being contracted into the subtraction)
@@ -313,6 +318,9 @@ __device__ __forceinline__ void sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Workgroups a CU to build for: what LDS and the accumulators allow. 256 points, 4,000 voxels (8 x 8 / 16 x 16 grid):
+// two 1,058 / 1,715 us, one 1,449 / 2,299; 96 and 128 points as two or one are within 6%; up to 64 points three
+// leave 168 registers (built for two, 64 points: 505 / 1,042 -> 483 / 969); the 512-point shape fills a CU's LDS.
 template <int NS>
 __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 ? 2 : 1))
     fit_strip_kernel(FitParams P, FitArgs io, const SlotRec* __restrict__ recs, const RotRec* __restrict__ rots,
@@ -323,9 +331,14 @@ __global__ void __launch_bounds__(64 * strip_waves(NS), NS <= 4 ? 3 : (NS <= 16 
   constexpr int N = NS * kStrip;
   constexpr bool kLds = strip_lds(NS);
   constexpr bool kTab = !kLds;              // separable query tables in LDS
-  constexpr int D = NS >= 32 ? 4 : (NS == 2 ? 1 : 2);  // tiles in flight
-  constexpr int kBatch = NS <= 8 ? 4 : 1;                          // rounds of queries written together
-  constexpr int H = NS >= 32 ? 4 : 0;                              // ... of the next column
+  // Tiles in flight, and those of the next column among them. Tiles in scratch need them: 512 points, 1,500 voxels
+  // (8 x 8 / 16 x 16 grid), D = 4 2,033 / 2,989 us, 2 2,101 / 3,174; 256 points with more than two spill, and one
+  // costs 7% / 9%. From LDS one to four are within 2%. H = 0 to 4 are within 1% at 512 points.
+  constexpr int D = NS >= 32 ? 4 : (NS == 2 ? 1 : 2);
+  constexpr int H = NS >= 32 ? 4 : 0;
+  // Rounds of queries written together, so that all lanes write: 20,000 voxels, 16 x 16 grid, four 458 and 1,042 us
+  // (32 and 64 points), one 472 and 1,067. Within the spread above 64 points.
+  constexpr int kBatch = NS <= 8 ? 4 : 1;
   // Voxels of up to 32 points are taken at a fixed stride: they are solved faster than the one counter gives
   // out numbers (~9 ns each; 20,000 voxels on an 8 x 8 grid 308 us, so 230). Larger ones are not, and differ
   // more (20,000 of 64 points: counter 595 us, stride 860).
