@@ -109,9 +109,10 @@ def bucket_of(n: np.ndarray) -> np.ndarray:
 def precision_split(n_kept: np.ndarray, solved: np.ndarray, m: int, tuning: dict, precision: str) -> dict:
     """Share of the step's algorithmic FLOPs computed in each arithmetic type, from
     the launch choices that ran: in FP32 and MIXED mode the buckets up to
-    fp32_last_bucket that are not tiled run in float (their voxels flagged for
-    re-solve again in double), tiled buckets run FP64 tiles (MIXED: FP32 tiles
-    and FP32 query products); everything else runs in double."""
+    fp32_last_bucket and below tile_first_bucket run in float (their voxels
+    flagged for re-solve again in double); in MIXED mode the buckets from
+    tile_first_bucket on run FP32 tiles and query products; everything else
+    runs in double."""
     b_of = bucket_of(n_kept)
     fl = voxel_flops(n_kept, m)
     share = {}

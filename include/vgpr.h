@@ -97,7 +97,7 @@ enum {
                           cond_threshold or the refinement score sum_j |y_j| / d_j exceeds
                           refine_threshold, two FP64 residual refinement steps of alpha
                           (status REFINED) */
-  VGPR_PREC_FP64 = 2   /* FP64 build and LDL^T for every voxel */
+  VGPR_PREC_FP64 = 2   /* FP64 build and factorisation for every voxel (LDL^T up to 16 points, L L^T above) */
 };
 
 /*

@@ -205,7 +205,6 @@ __device__ __forceinline__ void prep_frame(const FitParams& P, const FitArgs& io
                                         const double (&sums)[9]) {
   const double s0 = sums[0], s1 = sums[1], s2 = sums[2], a00 = sums[3], a01 = sums[4], a02 = sums[5],
                a11 = sums[6], a12 = sums[7], a22 = sums[8];
-  (void)off;
   const double inv_n = 1.0 / (double)n;
   const double m0 = s0 * inv_n, m1 = s1 * inv_n, m2 = s2 * inv_n;
   double A[3][3];
@@ -487,8 +486,8 @@ __global__ void zero_kernel(uint32_t* __restrict__ p, int n) {
   if (i < n) p[i] = 0u;
 }
 
-// Longest-first order of the tiled buckets' slots: a counting sort by kept point count,
-// descending, one workgroup per bucket. The tiled solvers hand out voxels in this order, so
+// Longest-first order of a bucket's slots: a counting sort by kept point count,
+// descending, one workgroup per bucket. The solvers hand out voxels in this order, so
 // the largest solves start first and the last ones to start are the shortest (list
 // scheduling by longest processing time). Slots with equal counts may come in any order;
 // every voxel is solved the same way whatever its position. One launch on the caller's
@@ -743,7 +742,8 @@ __constant__ constexpr Reciprocals kReciprocal = make_reciprocals();
 __device__ __forceinline__ int div_by(int e, uint32_t reciprocal) { return (int)((uint32_t)e * reciprocal >> 16); }
 
 // ---------------------------------------------------------------------------
-// 2a. wave solver: one voxel per wavefront, n <= min(NMAX, 64), m <= 64
+// 2a. wave solver: one voxel per wavefront, n <= NMAX; m <= 256 for NMAX 16 and 32 (four query
+// rows a lane), m <= 64 for NMAX 64
 //
 // Bound by vector issue: every step's column is one broadcast and one product a query row and
 // the data row, and few wavefronts are there to fill the gaps. So registers decide: with the
@@ -1005,13 +1005,6 @@ __global__ void __launch_bounds__(kWaveThreads) fit_wave_kernel(FitParams P, Fit
         const T y = bcast(fy, j);  // y_j = (L^-1 f~)_j, final once step j is reached
         const T inv = recip(d);
         const T tB = cjB * inv;
-        if constexpr (kRefine) {
-          if (lane == j) {
-            dself = d;
-            yself = y;
-          }
-          if (lane > j && lane < n) sL[j * NMAX + lane] = tB;  // K was read from this region before step 0
-        }
 #pragma unroll
         for (int r = 0; r < QR; ++r) {
           const T cjA = A[r][0];
@@ -2088,14 +2081,14 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
   // (bucket_stream of the launch choices; by default the 96/128-point buckets on
   // side stream 1, the 32/64-point buckets on side stream 2, the 256/512-point
   // buckets on side stream 3, the 16-point bucket and its passes on the caller's
-  // stream), joined back before the call returns (with tiled_first, the tiled
-  // buckets run before the fork instead). Many small voxels fill the CUs that
-  // the few long large-voxel solves leave idle.
+  // stream), joined back before the call returns. Many small voxels fill the CUs
+  // that the few long large-voxel solves leave idle.
   st = ensure_aux(ctx);
   if (st != VGPR_OK) return st;
   const vgpr_tuning& tu = ctx->tune;
-  // tiled_first: the tiled buckets run alone on the caller's stream before the
-  // fork (their workgroups need whole CUs, which concurrent buckets would hold)
+  // tiled_first: the buckets from tile_first_bucket on run alone on the caller's stream
+  // before the fork. Strips of up to 128 points share CUs, and it makes no difference to
+  // them (fit of 64 frames of 32 x 1800 points 772 / 773 us, of one frame 110 / 107).
   const bool tiles_first = tu.streams != 1 && tu.tiled_first != 0;
   auto stream_of = [&](int b) {
     if (tu.streams == 1 || (tiles_first && b >= first_tile_bucket(ctx))) return ctx->stream;
@@ -2166,7 +2159,7 @@ vgpr_status fit_predict_impl(vgpr_ctx* ctx, const FitArgs& a, const vgpr_params*
               a.n_vox < (int64_t(1) << 30);
   auto skipped = [&](int b) { return merge_top && b == kNumBuckets - 2; };
   {
-    // longest-first orders of the tiled buckets, one workgroup each
+    // longest-first orders, one workgroup a bucket
     OrderJobs oj{};
     int nj = 0;
     for (int b = 1; b < kNumBuckets; ++b) {

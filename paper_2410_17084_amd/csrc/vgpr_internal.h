@@ -18,7 +18,7 @@ constexpr int kKeyFieldBits = 21;
 constexpr int64_t kKeyBias = int64_t(1) << 20;
 constexpr int64_t kKeyAxisLimit = (int64_t(1) << 20) - 1;
 constexpr uint64_t kKeySentinel = ~uint64_t(0);
-constexpr int kMaxPtsLimit = 512;   // largest cap the tiled solver supports
+constexpr int kMaxPtsLimit = 512;   // largest cap the solvers support
 // Size of the fixed device scratch of vgpr_fit_predict_noalloc (one array per GPU).
 constexpr size_t kFixedScratchBytes = size_t(64) << 20;
 constexpr int kMaxGridSide = 16;
