@@ -675,7 +675,8 @@ extern "C" vgpr_status vgpr_structure_loss(vgpr_ctx* ctx, const float* d_pts, in
                o_arg = sub(d_arg ? 0 : 4 * (size_t)n), o_ts = sub(8 * (size_t)nt), o_tn = sub(4 * (size_t)nt),
                o_misc = sub(64);
   head = (head + 255) & ~size_t(255);
-  // the voxelizer's scratch, with 1 MB for its fixed parts that the open list's take some of
+  // with the voxelizer's scratch: 24 bytes a Gaussian and 1 MB for its fixed parts (under 100 KB), of which 32 KB
+  // make up for the fixed parts of the open list
   vgpr_status st = reserve_work(ctx, head + 24 * (size_t)ng + 4096 * 16 + (1 << 20) - (32 << 10));
   if (st != VGPR_OK) return st;
   st = reserve_pinned(ctx, 64);
